@@ -208,6 +208,7 @@ sos_status build_plan_tables(sos_plan_s &p, const double *sos) {
     }
   }
   int64_t W = lo + 1;
+  p.runin = W;
   const int64_t NL = (int64_t)N * p.L;
   p.warm = ((W + NL - 1) / NL) * NL;
   // the norm over the rounded length, for reporting
@@ -226,6 +227,7 @@ sos_status build_plan_tables(sos_plan_s &p, const double *sos) {
     }
     p.warm_norm = have ? inf_norm(r, D) : 1.0;
   }
+  if (strip_supported(p)) p.phi_pow = std::move(pw);
   return SOS_OK;
 }
 

@@ -79,6 +79,13 @@ struct sos_plan_s {
   void *d_aop = nullptr;
   // exact inter-tile carry: the one-step state transition phi on the device
   void *d_phi = nullptr;
+  // strip path (sosfilt_strip.hip): the run-in before rounding to groups,
+  // the powers phi^(2^j) of the run-in search, the device tables
+  int64_t runin = 0;
+  std::vector<std::vector<double>> phi_pow;
+  double *d_strip = nullptr;
+  int strip_span = 0;              // samples the state table covers (a multiple of 16)
+  size_t strip_g = 0, strip_phi = 0;   // doubles from d_strip to the all-pole responses and the powers
 };
 
 namespace sosf {
@@ -116,6 +123,15 @@ bool wide_plan(const sos_plan_s &p);
 int64_t wide_tile(const sos_plan_s &p, int64_t n);
 size_t wide_workspace(const sos_plan_s &p, int64_t n);
 sos_status launch_wide(const sos_plan_s &p, const void *x, void *y, int64_t n, void *ws, hipStream_t s);
+// strips (sosfilt_strip.hip): whether a plan has the tables, the geometry of
+// n samples in strips of about len, whether a single signal takes them (tile,
+// scan: what the tile kernels would run), the launches
+bool strip_supported(const sos_plan_s &p);
+sos_status upload_strip(sos_plan_s &p);
+struct StripChan;
+bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, StripChan &c);
+bool strip_single(const sos_plan_s &p, int64_t n, int64_t tile, bool scan, StripChan &c);
+sos_status launch_strip(const sos_plan_s &p, const StripChan &c, const void *x, void *y, hipStream_t s);
 // narrow groups, N = 4 (sosfilt_narrow.hip): single signals on 16-lane rows
 bool narrow_plan(const sos_plan_s &p);
 }

@@ -14,6 +14,7 @@
 #include "kernels_block.hpp"
 #include "kernels_wide.hpp"
 #include "plan.hpp"
+#include "strip_types.hpp"
 
 using namespace sosf;
 
@@ -332,6 +333,7 @@ sos_status create_plan(const double *sos, int32_t K, const sos_opts *opts, bool 
   }
   if (st == SOS_OK && !(o.flags & SOS_FLAG_HOST_ONLY)) {
     st = upload(*p);
+    if (st == SOS_OK && strip_supported(*p)) st = upload_strip(*p);
     if (st == SOS_OK && carry_supported(*p)) {
       // the transition the exact inter-tile carry raises to the tile length
       const size_t bytes = p->phi.size() * sizeof(double);
@@ -387,6 +389,7 @@ sos_status sos_plan_destroy(sos_plan_t p) {
     if (p->d_block) hipFree(p->d_block);
     if (p->d_aop) hipFree(p->d_aop);
     if (p->d_phi) hipFree(p->d_phi);
+    if (p->d_strip) hipFree(p->d_strip);
     if (p->device >= 0 && cur >= 0 && cur != p->device) hipSetDevice(cur);
   }
   if (p->bwd) sos_plan_destroy(p->bwd);
@@ -496,6 +499,9 @@ sos_status sos_filt(sos_plan_t p, const void *x, void *y, int64_t n, void *works
   // the exact inter-tile carry where the run-in would cost more than the
   // carry's second pass (it needs the caller's workspace)
   const CarryLayout cl = carry_layout(*p, n, a.tile);
+  // long signals: one lane per strip of the time axis (no workspace)
+  StripChan sc;
+  if (strip_single(*p, n, a.tile, cl.use, sc)) return launch_strip(*p, sc, x, y, s);
   if (cl.use) {
     if (workspace && ((uintptr_t)workspace & 15) == 0) return launch_carry(*p, cl, x, y, n, workspace, s);
     if (p->flags & SOS_FLAG_CARRY_SCAN) return SOS_E_ARG;   // asked for, but no workspace

@@ -1,0 +1,206 @@
+// Strip path (kernels_strip.hpp): its tables, its geometry and its launches.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <vector>
+
+#include "dispatch.hpp"
+#include "kernels_strip.hpp"
+#include "plan.hpp"
+
+using namespace sosf;
+
+namespace sosf {
+
+bool strip_supported(const sos_plan_s &p) {
+  return p.solver_opt == SOS_AUTO && p.compute_dtype == SOS_F64 && p.L == kL && p.N >= 8 && p.N <= 64 &&
+         p.K <= kStripMaxK && p.b0_factored && p.tile_groups == 0 &&
+         !(p.flags & (SOS_FLAG_CARRY_SCAN | SOS_FLAG_CARRY_RUNIN));
+}
+
+// Device tables: the state table, the all-pole responses and the padded
+// powers of the transition.
+//   state table: entry (row i, j) is the response of state value i at a
+//     strip's end to the raw input j samples before the end, h_k[j - d] with
+//     k = i / 2 and d = 1 for even rows (y[-2]), 0 for odd ones (y[-1]);
+//     block b, row i, element e holds j = 16 b + 15 - e (ascending time), so
+//     that a lane's four MFMA A operands are consecutive;
+//   all-pole responses g_k: section k's output to a unit input of the first
+//     section's recursive part (h_k = g_k + b1 g_k[. - 1] + b2 g_k[. - 2]).
+sos_status upload_strip(sos_plan_s &p) {
+  const int K = p.K, D = 2 * K, mt = (D + 15) / 16, R = 16 * mt;
+  const int span = (int)std::min<int64_t>((p.runin + 31) / 32 * 32, kStripMaxSpan);
+  const int gs = span + 16;
+  const size_t hop = (size_t)span * R, gsz = (size_t)K * gs, psz = p.phi_pow.size() * (size_t)R * R;
+  std::vector<double> t(hop + gsz + psz, 0.0);
+  double *g = t.data() + hop, *ph = g + gsz;
+  // every section per sample, so that the sections' recurrences overlap
+  std::vector<double> state(4 * (size_t)K, 0.0);   // per section: input x1, x2, output y1, y2
+  for (int j = 0; j < gs; ++j) {
+    double v = j == 0 ? 1.0 : 0.0;   // the first section's recursive part takes it as it is
+    for (int k = 0; k < K; ++k) {
+      const double *o = &p.rows[5 * k];
+      double *z = &state[4 * (size_t)k];
+      if (k > 0) {
+        const double x0 = v;
+        v = x0 + o[1] * z[0] + o[2] * z[1];
+        z[1] = z[0];
+        z[0] = x0;
+      }
+      v -= o[3] * z[2] + o[4] * z[3];
+      z[3] = z[2];
+      z[2] = v;
+      g[(size_t)k * gs + j] = v;
+    }
+  }
+  const double b1 = p.rows[1], b2 = p.rows[2];
+  std::vector<double> h(span + 1);
+  for (int k = 0; k < K; ++k) {
+    const double *gk = g + (size_t)k * gs;
+    h[0] = 0.0;   // h[l + 1] = h_k[l]
+    h[1] = gk[0];
+    if (span > 1) h[2] = gk[1] + b1 * gk[0];
+    for (int l = 2; l < span; ++l) h[l + 1] = gk[l] + b1 * gk[l - 1] + b2 * gk[l - 2];
+    for (int b = 0; b < span / 16; ++b) {
+      double *even = &t[((size_t)b * R + 2 * k) * 16], *odd = even + 16;
+      const double *hb = &h[16 * b];
+      for (int e = 0; e < 16; ++e) {
+        even[e] = hb[15 - e];   // d = 1: h_k[j - 1]
+        odd[e] = hb[16 - e];    // d = 0: h_k[j]
+      }
+    }
+  }
+  for (size_t q = 0; q < p.phi_pow.size(); ++q)
+    for (int i = 0; i < D; ++i)
+      for (int j = 0; j < D; ++j) ph[q * R * R + (size_t)i * R + j] = p.phi_pow[q][(size_t)i * D + j];
+  if (hipMalloc(&p.d_strip, t.size() * sizeof(double)) != hipSuccess) {
+    p.d_strip = nullptr;
+    return SOS_E_NOMEM;
+  }
+  if (hipMemcpy(p.d_strip, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
+    return SOS_E_DEVICE;
+  p.strip_span = span;
+  p.strip_g = hop;
+  p.strip_phi = hop + gsz;
+  return SOS_OK;
+}
+
+// Strips of about `len` samples over [-shift, n).
+bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, StripChan &c) {
+  if (!p.d_strip) return false;
+  const int64_t es = p.io_dtype == SOS_F64 ? 8 : 4;
+  const int mt = (2 * p.K + 15) / 16;
+  // samples of one state area with its alignment; a strip holds two, and the lead
+  const int64_t area = (16 * mt * 8 + 16) / es, least = 3 * area + 32;
+  // The state table covers the run-in, so a strip that long needs one term;
+  // shorter strips are powers of two (their transition is a table entry), at
+  // most 2 KB, so that a long signal has two wavefronts per SIMD.
+  const bool covers = p.runin <= p.strip_span && len >= p.strip_span;
+  if (covers) {
+    // (off the multiples of 2 KB: strips a power of two apart meet in few HBM
+    // channels; K = 3 on 2^26 FP32 samples, 1024 a strip: 167 us, 1184: 132)
+    len = (len + 31) / 32 * 32;
+    if (len * es % 2048 == 0) len += 32;
+  } else {
+    const int64_t most = 2048 / es;
+    int64_t l = 32;
+    while (2 * l <= len || l < least) l *= 2;
+    len = std::min(l, most);
+    if (len > p.strip_span || len < least || (p.runin + len - 1) / len > kStripMaxTerms) return false;
+  }
+  const int64_t rem = (n + shift) % len;
+  const int64_t lead = rem > 0 && rem < area ? (area - rem + 31) / 32 * 32 : 0;
+  c.tab = static_cast<const double *>(p.d_table);
+  c.hop = p.d_strip;
+  c.g = p.d_strip + p.strip_g;
+  c.phi = p.d_strip + p.strip_phi;
+  c.off = 0;
+  c.n = n;
+  c.len = len;
+  c.strips = (n + shift + lead + len - 1) / len;
+  c.first_item = 0;
+  c.K = p.K;
+  c.stride = p.stride;
+  c.shift = shift;
+  c.span = (int32_t)(covers ? p.strip_span : len);
+  c.terms = covers ? 1 : (int32_t)((p.runin + len - 1) / len);
+  c.mt = mt;
+  c.gstride = p.strip_span + 16;
+  c.lead = (int32_t)lead;
+  c.gain = p.gain;
+  // 32-bit byte offsets, with the strips past the end
+  return (n + 96 * len) * es < ((int64_t)1 << 32);
+}
+
+// Strips for a single signal of n samples, where they beat the tile kernels.
+// Measured against PH at N = 64 (MI355X, us, tiles / strips):
+//   FP32 I/O, K = 8 (r <= 0.98): 7e6 samples 43 / 53, 1.2e7 66 / 53, 3.3e7
+//     121 / 90, 1e8 325 / 245; K = 3: 1.2e7 45 / 43, 3.3e7 97 / 71; K = 12:
+//     2e7 124 / 147, 3.3e7 152 / 125, 1e8 408 / 288;
+//   FP64 I/O, K = 8: 3e6 53 / 40, 2^24 + 5 148 / 88, 5e7 300 / 279; K = 3:
+//     1.2e7 64 / 72, 2.5e7 122 / 145; K = 12: 2.5e7 182 / 191, 5e7 340 / 279;
+//   poles up to r = 0.999, where the tiles carry by the scan or run in over
+//     more than a tile (K = 8): FP32 3e6 59 / 56, 1.2e7 114 / 64, FP64 3e6
+//     62 / 48, 2^24 + 5 204 / 101.
+// With FP32 I/O the tiles keep signals that they share out evenly in powers of
+// two, where they are at their best (2^26: 175 us against 236; 2^28, launch
+// after launch: 611 against 618).
+bool strip_single(const sos_plan_s &p, int64_t n, int64_t tile, bool scan, StripChan &c) {
+  if (!p.d_strip) return false;
+  const bool f64 = p.io_dtype == SOS_F64, slow = scan || p.warm > tile;
+  const int64_t least = slow ? 3000000
+                             : (f64 ? (p.K <= 4 ? INT64_MAX : (p.K <= 8 ? 1 << 21 : 40000000))
+                                    : (p.K <= 8 ? 10000000 : 30000000));
+  if (n < least) return false;
+  const int64_t lanes = (int64_t)p.simds * 64, len = (n + lanes - 1) / lanes;
+  const bool covers = p.runin <= p.strip_span && len >= p.strip_span;
+  const int64_t groups = tile / ((int64_t)p.N * p.L);
+  if (!f64 && !slow && (groups & (groups - 1)) == 0 && n % (tile * 4 * p.simds) == 0) return false;
+  // shorter strips than the run-in are powers of two: down to 7/8 of a
+  // wavefront per SIMD rather than twice as many
+  return strip_geometry(p, n, 0, covers ? len : len * 8 / 7, c);
+}
+
+namespace {
+
+template <typename TI, int MT>
+sos_status launch(const StripArgs &a, int64_t items, int terms, int K, const void *x, void *y, hipStream_t s) {
+  const TI *xi = static_cast<const TI *>(x);
+  TI *yi = static_cast<TI *>(y);
+  const unsigned blocks = (unsigned)((items + kWavesPerBlock - 1) / kWavesPerBlock);
+  if (terms == 1)
+    hipLaunchKernelGGL((strip_state_kernel<TI, MT, false>), dim3(blocks), dim3(256), 0, s, xi, yi, a);
+  else
+    hipLaunchKernelGGL((strip_state_kernel<TI, MT, true>), dim3(blocks), dim3(256), 0, s, xi, yi, a);
+  if (terms > 16)
+    hipLaunchKernelGGL((strip_scan_kernel<TI, MT>), dim3((unsigned)items), dim3(256), 0, s, yi, a);
+#define SOSF_STRIP_FILTER(KT)                                                                             \
+  hipLaunchKernelGGL((strip_filter_kernel<TI, KT>), dim3(blocks), dim3(256), strip_lds_bytes<TI>(K), s, xi, yi, a, \
+                     (int32_t)K)
+  switch (K) {
+    case 1: SOSF_STRIP_FILTER(1); break;
+    case 2: SOSF_STRIP_FILTER(2); break;
+    case 3: SOSF_STRIP_FILTER(3); break;
+    case 4: SOSF_STRIP_FILTER(4); break;
+    case 5: SOSF_STRIP_FILTER(5); break;
+    case 6: SOSF_STRIP_FILTER(6); break;
+    case 7: SOSF_STRIP_FILTER(7); break;
+    case 8: SOSF_STRIP_FILTER(8); break;
+    default: SOSF_STRIP_FILTER(0); break;
+  }
+#undef SOSF_STRIP_FILTER
+  return hipGetLastError() == hipSuccess ? SOS_OK : SOS_E_DEVICE;
+}
+
+}  // namespace
+
+sos_status launch_strip(const sos_plan_s &p, const StripChan &c, const void *x, void *y, hipStream_t s) {
+  StripArgs a{};
+  a.items = (c.strips + kStripLanes - 1) / kStripLanes;
+  a.one = c;
+  if (p.io_dtype == SOS_F32)
+    return c.mt == 1 ? launch<float, 1>(a, a.items, c.terms, p.K, x, y, s) : launch<float, 2>(a, a.items, c.terms, p.K, x, y, s);
+  return c.mt == 1 ? launch<double, 1>(a, a.items, c.terms, p.K, x, y, s) : launch<double, 2>(a, a.items, c.terms, p.K, x, y, s);
+}
+
+}  // namespace sosf

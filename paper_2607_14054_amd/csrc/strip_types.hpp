@@ -1,0 +1,42 @@
+// Descriptors of the strip kernels (kernels_strip.hpp), shared by the plan
+// and the launches.
+#pragma once
+
+#include <cstdint>
+
+#include <hip/hip_runtime.h>
+
+namespace sosf {
+
+constexpr int kStripBlock = 16;          // samples per block of the state table
+constexpr int kStripMaxSpan = 1024;      // samples the state table covers at most
+constexpr int kStripMaxK = 16;           // 2K state rows fit two 16-row tiles
+constexpr int kStripMaxTerms = 512;      // strips a start state is summed over at most
+constexpr int kStripLanes = 64;          // strips per wavefront of the filter kernel
+
+// A channel (or a single signal) cut into strips of `len` samples over
+// [-shift - lead, n); strip s starts at s * len - lead - shift.  The samples
+// before 0 are zeros; the lead, a multiple of 32 below len, keeps the last
+// strip long enough for its start state.
+struct StripChan {
+  const double *tab;       // the plan's section rows
+  const double *hop;       // state table, [block][row][16]: see build_strip_tables
+  const double *g;         // all-pole responses, [K][gstride]
+  const double *phi;       // padded powers Phi^(2^j), [j][16 MT][16 MT]
+  int64_t off, n;          // first sample in x / y, length
+  int64_t len, strips;     // samples per strip (a multiple of 32; a power of two where terms > 1), strips
+  int64_t first_item;      // first work item (64 strips) of the channel
+  int32_t K, stride;
+  int32_t shift;           // off mod the samples per 16 bytes
+  int32_t span;            // samples of a strip that its end state is summed over (a multiple of 16)
+  int32_t terms;           // strips whose end states reach into the next strip's start
+  int32_t mt;              // 16-row tiles of the state: ceil(2K / 16)
+  int32_t gstride;         // doubles per row of g
+  int32_t lead;            // zero samples before the aligned start
+  int32_t pad;
+  double gain;
+};
+
+static_assert(sizeof(StripChan) % 8 == 0, "copied by 64-bit words");
+
+}  // namespace sosf
