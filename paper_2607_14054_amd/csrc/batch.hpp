@@ -9,6 +9,7 @@
 #include "adjoint_types.hpp"
 #include "plan.hpp"
 #include "dispatch.hpp"
+#include "strip_types.hpp"
 
 struct sos_batch_s {
   int C = 0, N = 0, L = 16, io_dtype = SOS_F32, compute_dtype = SOS_F64;
@@ -24,6 +25,15 @@ struct sos_batch_s {
   std::vector<int32_t> order;             // channels in launch order
   std::vector<sosf::BatchChan> chans;     // in launch order
   std::vector<int32_t> item_chan;         // item -> index into chans
+  // channels filtered by strips (kernels_strip.hpp): the rest of the channels'
+  // items are `rows_items`; items, tile and order stay the tile kernels'
+  // schedule of every channel
+  int64_t rows_items = 0, strip_items = 0;
+  bool strip_scan = false;                // a channel's run-in reaches over more than 16 strips
+  std::vector<sosf::StripChan> strip_chans;
+  std::vector<int32_t> strip_item_chan;   // strip item -> index into strip_chans
+  sosf::StripChan *d_strips = nullptr;
+  int32_t *d_strip_item = nullptr;
   sosf::BatchChan *d_chans = nullptr;
   int32_t *d_item_chan = nullptr;
   // adjoint schedule (device batches whose plans carry the adjoint)
@@ -41,8 +51,8 @@ struct sos_batch_s {
   // every device descriptor lives in one allocation (and its pinned host
   // staging copy, for sos_batch_replan), at offsets fixed when the batch is
   // created: a launch captured in a HIP graph stays valid after a replan.
-  // The allocation starts with a header of two int64: the forward launch's
-  // live item count and the schedule's generation.
+  // The allocation starts with a header of four int64: the forward launch's
+  // live item count, the schedule's generation, the live strip items.
   unsigned char *d_blob = nullptr, *h_blob = nullptr;
   size_t blob_cap = 0;
   hipEvent_t copied = nullptr;            // the last staging upload has been read
@@ -51,6 +61,8 @@ struct sos_batch_s {
   // kernel instance (b0 factoring, solver class)
   int32_t C_cap = 0, kmax_cap = 0;
   int64_t items_cap = 0, adj_items_cap = 0, rows_cap = 0;
+  int64_t strip_cap = 0, strip_rows_cap = 0;   // strip and tile items of the launch (0 strips: tile kernels only)
+  bool strip_scan_cap = false;            // the launch includes the strips' scan
   bool inst_b0one = true;
   int inst_mix = SOS_PH;
   int64_t gen = 0;                        // schedule generation (header[1])
@@ -61,6 +73,11 @@ struct sos_batch_s {
 bool batch_descriptors_valid(const sos_batch_s &b);
 
 namespace sosf {
+// strips in a batch (sosfilt_strip.hip): moves the channels that gain from
+// the tiles' schedule to the strips'; back to the tiles; the launches
+void strip_schedule(sos_batch_s &b, const sos_plan_t *plans);
+void strip_unschedule(sos_batch_s &b);
+sos_status launch_strip_batched(const sos_batch_s &b, const void *x, void *y, hipStream_t s);
 // the adjoint schedule, host side (sosfilt_backward.hip)
 sos_status schedule_batch_adjoint(sos_batch_s &b, const sos_plan_t *plans, int32_t tile_groups);
 // batched block filtering (sosfilt_block.hip)

@@ -83,6 +83,23 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t strip_rsrc(const TI *p, const 
                                            (int)(uint32_t)((c.n + c.shift) * (int64_t)sizeof(TI)), 0x00020000);
 }
 
+// 128 bytes of each strip (32 samples, FP64: 16) move between HBM and the
+// lanes through a per-wave LDS tile of one row per strip.  Global accesses
+// are 16-byte vectors, the 8 lanes of a strip covering its line; the 16-byte
+// pieces of a row are permuted by the strip's index so that the 16 lanes that
+// read or write the same piece of their rows fall on distinct banks.
+template <typename TI>
+struct StripStage {
+  typedef typename Vec16<TI>::type VT;
+  static constexpr int V = Vec16<TI>::n;
+  static constexpr int C = 128 / (int)sizeof(TI);    // samples per chunk: a 128-byte line per strip
+  static constexpr int PIECES = C / V;               // 16-byte pieces per row
+  static constexpr int ROWS = 64 / PIECES;           // rows per wave-wide access
+  static constexpr int OPS = PIECES;                 // accesses per tile
+  static constexpr int BYTES = 64 * 128;
+  static __device__ __forceinline__ int slot(int s, int p) { return s * PIECES + (p ^ ((s >> 1) & 7)); }
+};
+
 // Rotates a value d lanes up inside its 16-lane row (d = 1, 2, 4, 8).
 template <int D>
 __device__ __forceinline__ double row_ror(double v) {
@@ -116,16 +133,14 @@ __device__ __forceinline__ void strip_round(sv4d (&v)[NT][MT], const double (&P)
         v[t][m] = __builtin_amdgcn_mfma_f64_16x16x4f64(P[m][k], sh[t][k / 4][k % 4], v[t][m], 0, 0, 0);
 }
 
-// Phi^(2^j), padded, in the A operand's layout.
+// Phi^(2^j), padded, in the A operand's layout (as the table holds it).
 template <int MT>
-__device__ __forceinline__ void strip_power(double (&P)[MT][4 * MT], const double *__restrict__ phi, int j, int i,
-                                            int q) {
-  constexpr int D = 16 * MT;
-  const gptr<double> f = (gptr<double>)(phi + (int64_t)j * (D * D));
+__device__ __forceinline__ void strip_power(double (&P)[MT][4 * MT], const double *__restrict__ phi, int j) {
+  const gptr<double> f = (gptr<double>)(phi + (int64_t)j * (256 * MT * MT) + lane_id());
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int k = 0; k < 4 * MT; ++k) P[m][k] = f[(16 * m + i) * D + 4 * k + q];
+    for (int k = 0; k < 4 * MT; ++k) P[m][k] = f[(m * 4 * MT + k) * 64];
 }
 
 // Start states of 64 strips per wavefront, in 16-strip tiles.  MFMA operands
@@ -145,26 +160,25 @@ __device__ __forceinline__ void strip_power(double (&P)[MT][4 * MT], const doubl
 // samples per step a step lasts 2560 cycles (MT = 1), which is what the next
 // step's loads have to arrive.
 template <typename TI, int MT, bool SCAN>
-__global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_state_kernel(const TI *__restrict__ xs,
-                                                                          TI *__restrict__ ys, StripArgs a) {
-  constexpr int H = SCAN ? 1 : 0, NT = 4 + H, V = Vec16<TI>::n, XP = 4 / V;
+__device__ __forceinline__ void strip_state(const TI *__restrict__ xs, TI *__restrict__ ys, const StripChan &c,
+                                            int s0, unsigned char *lds) {
+  typedef StripStage<TI> St;
+  typedef typename St::VT VT;
+  constexpr int H = SCAN ? 1 : 0, NT = 4 + H, V = St::V, XP = 4 / V;
   constexpr int U = 8 / (int)sizeof(TI);   // 16-sample blocks per step: a 128-byte line per strip
-  constexpr int BUFS = MT == 1 ? 3 : 2;
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + w;
-  StripChan c;
-  if (!strip_item(a, item, c) || c.mt != MT || (c.terms > 1) != SCAN) return;
-  const int s0 = (int)((item - c.first_item) * kStripLanes);
+  constexpr int OPS = 16 * NT / St::ROWS;  // accesses per step
   const int lane = lane_id(), i = lane & 15, q = lane >> 4;
   const __amdgpu_buffer_rsrc_t rx = strip_rsrc(xs, c);
   const int es = (int)sizeof(TI), len = (int)c.len;
-  // byte offset of the lane's four samples of block 0 of its strip in tile t
-  // (strips before the channel wrap past the buffer's end: zeros)
-  uint32_t at[NT];
+  // byte offset of the lane's piece of op j (strips before the channel wrap
+  // past the buffer's end: zeros)
+  VT *stage = reinterpret_cast<VT *>(lds);
+  uint32_t at[OPS];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int s = s0 + 16 * (t - H) + i;
-    at[t] = (uint32_t)(s * len - c.lead + (len - c.span) + 4 * q) * (uint32_t)es;
+  for (int j = 0; j < OPS; ++j) {
+    const int row = j * St::ROWS + lane / St::PIECES;
+    at[j] = (uint32_t)((s0 - 16 * H + row) * len - c.lead + (len - c.span)) * (uint32_t)es +
+            16u * (uint32_t)(St::slot(row, lane % St::PIECES) - row * St::PIECES);
   }
   sv4d acc[NT][MT];
 #pragma unroll
@@ -172,81 +186,83 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_state_kernel(con
 #pragma unroll
     for (int m = 0; m < MT; ++m) acc[t][m] = sv4d{0.0, 0.0, 0.0, 0.0};
   const int blocks = c.span / kStripBlock;
-  const gptr<double> hp = (gptr<double>)(c.hop + (int64_t)(blocks - 1) * (MT * 256) + i * 16 + 4 * q);
+  const gptr<vd2> hp = (gptr<vd2>)(c.hop) + (int64_t)(blocks - 1) * (MT * 128) + lane;
   struct Step {
-    typename Vec16<TI>::type x[NT][U][XP];
+    sv4u in[OPS];
     vd2 h[MT][U][2];
   };
-  auto fetch = [&](Step &f, int b) {
+  auto fetch = [&](Step &f, int n) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int j = 0; j < OPS; ++j)
+      f.in[j] = __builtin_bit_cast(sv4u, __builtin_amdgcn_raw_buffer_load_b128(rx, at[j] + 128u * (uint32_t)n, 0, 0));
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int k = 0; k < XP; ++k)
-          f.x[t][u][k] = __builtin_bit_cast(
-              typename Vec16<TI>::type,
-              __builtin_amdgcn_raw_buffer_load_b128(rx, at[t] + (uint32_t)(16 * (b + u) * es + 16 * k), 0, 0));
+    for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
-          f.h[m][u][k] = *(gptr<vd2>)(hp - (int64_t)(b + u) * (MT * 256) + m * 256 + 2 * k);
-    }
+        for (int k = 0; k < 2; ++k) f.h[m][u][k] = hp[(m * 2 + k) * 64 - (int64_t)(U * n + u) * (MT * 128)];
   };
-  auto use = [&](const Step &f) {
+  // the step of strip 0 that starts with the channel's start: the samples
+  // before it in the same 16 bytes are zeros
+  const int head = s0 == 0 && c.shift > 0 ? (c.lead - (len - c.span)) / (16 * U) : -1;   // uniform
+  // Through the tile, so that adjacent lanes load adjacent addresses (a load of
+  // 16 bytes from each of 64 places takes 64 cycles of the texture unit, which
+  // bound this kernel before: 135 us for 64 x 2^20 samples).
+  auto use = [&](const Step &f, int n) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int j = 0; j < OPS; ++j) stage[j * 64 + lane] = __builtin_bit_cast(VT, f.in[j]);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      double xd[NT][4];
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int k = 0; k < XP; ++k) {
+          const VT v = stage[St::slot(16 * t + i, (4 * u * XP) + q * XP + k)];
+#pragma unroll
+          for (int e = 0; e < V; ++e) xd[t][k * V + e] = (double)v[e];
+        }
+      if (u == 0 && n == head) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) xd[H][k] = lane == 0 && k < c.shift ? 0.0 : xd[H][k];
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
           for (int t = 0; t < NT; ++t)
-            acc[t][m] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.h[m][u][e / 2][e % 2], (double)f.x[t][u][e / V][e % V],
-                                                             acc[t][m], 0, 0, 0);
+            acc[t][m] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.h[m][u][e / 2][e % 2], xd[t][e], acc[t][m], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_wave_barrier();
   };
-  // the block of strip 0 that holds the channel's start: the samples before
-  // it in the same 16 bytes are zeros
-  const int head = s0 == 0 && c.shift > 0 ? (c.lead - (len - c.span)) / 16 : -1;   // uniform; even
-  auto mask = [&](Step &f, int b) {
-    const bool on = b == head && lane == 0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) f.x[H][0][k / V][k % V] = on && k < c.shift ? TI(0) : f.x[H][0][k / V][k % V];
-  };
-  // BUFS - 1 steps in flight, fetched without branches (past the last step the
-  // last one again), so that each wait covers its own step's loads only
-  Step f[BUFS];
+  // Two steps in flight, fetched without branches (past the last step the
+  // last one again), so that each wait covers its own step's loads only.
   const int steps = blocks / U;
-#pragma unroll
-  for (int u = 0; u < BUFS - 1; ++u) {
-    fetch(f[u], U * (u < steps ? u : steps - 1));
-    __builtin_amdgcn_sched_barrier(0);
-  }
+  Step f[2];
+  fetch(f[0], 0);
+  __builtin_amdgcn_sched_barrier(0);
   int n = 0;
-  for (; n + BUFS <= steps; n += BUFS) {
-#pragma unroll
-    for (int u = 0; u < BUFS; ++u) {
-      const int next = n + u + BUFS - 1;
-      fetch(f[(u + BUFS - 1) % BUFS], U * (next < steps ? next : steps - 1));
-      __builtin_amdgcn_sched_barrier(0);
-      mask(f[u], U * (n + u));
-      use(f[u]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  for (; n + 2 <= steps; n += 2) {
+    fetch(f[1], n + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    use(f[0], n);
+    fetch(f[0], n + 2 < steps ? n + 2 : steps - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    use(f[1], n + 1);
   }
-#pragma unroll
-  for (int u = 0; u < BUFS - 1; ++u)
-    if (n + u < steps) {
-      mask(f[u], U * (n + u));
-      use(f[u]);
-    }
+  if (n < steps) use(f[0], n);
   if constexpr (SCAN) {
-    // Phi^(len 2^j) for the rounds the run-in needs (past its end, the last one)
-    double P[4][MT][4 * MT];
+    // Phi^(len 2^j) for the rounds the run-in needs (past its end, the first
+    // one again), all at once where they fit the registers
+    constexpr int PN = MT == 1 ? 4 : 1;
+    double P[PN][MT][4 * MT];
     const int lg = 31 - __builtin_clz((unsigned)len);   // len = 2^lg
 #pragma unroll
-    for (int j = 0; j < 4; ++j) strip_power<MT>(P[j], c.phi, lg + (c.terms > (1 << j) ? j : 0), i, q);
+    for (int j = 0; j < PN; ++j) strip_power<MT>(P[j], c.phi, lg + (c.terms > (1 << j) ? j : 0));
     // the raw input's history: x[t0-2] and x[t0-1] enter through the first
     // section's non-recursive stage only (b2, and b1 then b2)
     const ctab<double> tab = as_ctab(c.tab);
@@ -279,9 +295,18 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_state_kernel(con
     }
     // sums over 2, 4, 8, 16 strips, as far as the run-in reaches
     strip_round<1, NT, MT>(acc, P[0], i);
-    if (c.terms > 2) strip_round<2, NT, MT>(acc, P[1], i);
-    if (c.terms > 4) strip_round<4, NT, MT>(acc, P[2], i);
-    if (c.terms > 8) strip_round<8, NT, MT>(acc, P[3], i);
+    if (c.terms > 2) {
+      if (PN == 1) strip_power<MT>(P[0], c.phi, lg + 1);
+      strip_round<2, NT, MT>(acc, P[1 % PN], i);
+    }
+    if (c.terms > 4) {
+      if (PN == 1) strip_power<MT>(P[0], c.phi, lg + 2);
+      strip_round<4, NT, MT>(acc, P[2 % PN], i);
+    }
+    if (c.terms > 8) {
+      if (PN == 1) strip_power<MT>(P[0], c.phi, lg + 3);
+      strip_round<8, NT, MT>(acc, P[3 % PN], i);
+    }
   }
   // the sum up to strip s is the state at the start of strip s + 1; sums that
   // need more than 16 strips go next to it, in strip s, for the scan kernel
@@ -299,6 +324,49 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_state_kernel(con
   }
 }
 
+constexpr int kStripStateLds = 80 * 128;   // bytes per wave: a line of five tiles' strips
+
+// Single signals: the instance of the cascade's size and the strips' length.
+template <typename TI, int MT, bool SCAN>
+__global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_state_kernel(const TI *__restrict__ xs,
+                                                                             TI *__restrict__ ys, StripArgs a) {
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + w;
+  StripChan c;
+  if (!strip_item(a, item, c)) return;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kWavesPerBlock * kStripStateLds];
+  strip_state<TI, MT, SCAN>(xs, ys, c, (int)((item - c.first_item) * kStripLanes), smem + w * kStripStateLds);
+}
+
+// Workgroup b of a batch's launch, so that eight in a row share an XCD (the
+// hardware deals workgroups out to the eight XCDs in turn) and, with it, the
+// channel's tables in its L2.
+__device__ __forceinline__ int64_t strip_block() {
+  const int b = (int)blockIdx.x, whole = (int)gridDim.x / 64 * 64;
+  return b < whole ? b / 64 * 64 + b % 8 * 8 + b % 64 / 8 : b;
+}
+
+// Batches: a branch per wavefront on the channel's instance.
+template <typename TI>
+__global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_state_batched_kernel(const TI *__restrict__ xs,
+                                                                                     TI *__restrict__ ys,
+                                                                                     StripArgs a) {
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t item = strip_block() * kWavesPerBlock + w;
+  StripChan c;
+  if (!strip_item(a, item, c)) return;
+  const int s0 = (int)((item - c.first_item) * kStripLanes);
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kWavesPerBlock * kStripStateLds];
+  unsigned char *lds = smem + w * kStripStateLds;
+  if (c.mt == 1) {
+    if (c.terms > 1) strip_state<TI, 1, true>(xs, ys, c, s0, lds);
+    else strip_state<TI, 1, false>(xs, ys, c, s0, lds);
+  } else {
+    if (c.terms > 1) strip_state<TI, 2, true>(xs, ys, c, s0, lds);
+    else strip_state<TI, 2, false>(xs, ys, c, s0, lds);
+  }
+}
+
 // Start states from sums over 16 strips, where the run-in reaches further:
 // with Q = Phi^(16 len), S_s = e_{s-1} + Q (e_{s-17} + Q (e_{s-33} + ...)),
 // 16 strips per wavefront.
@@ -308,6 +376,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void strip_scan_kernel(TI *__r
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t wave = (int64_t)blockIdx.x * kWavesPerBlock + w;
   StripChan c;
+  // (a batch launches both MT)
   if (!strip_item(a, wave / PER, c) || c.mt != MT || c.terms <= 16) return;
   const int s0 = (int)((wave / PER - c.first_item) * kStripLanes + (wave % PER) * 16);
   if (s0 >= c.strips) return;
@@ -324,7 +393,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void strip_scan_kernel(TI *__r
   sv4d acc[MT], nx[MT];
   sum_of(acc, s - 1 - 16 * (hops - 1));
   double P[MT][KS];
-  strip_power<MT>(P, c.phi, 31 - __builtin_clz((unsigned)c.len) + 4, i, q);
+  strip_power<MT>(P, c.phi, 31 - __builtin_clz((unsigned)c.len) + 4);
   for (int r = hops - 2; r >= 0; --r) {
     sum_of(nx, s - 1 - 16 * r);
 #pragma unroll
@@ -346,30 +415,9 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void strip_scan_kernel(TI *__r
 
 // ------------------------------------------------------------ filter pass
 
-// 128 bytes of each of 64 strips (32 samples, FP64: 16) move between HBM and
-// the lanes through a per-wave LDS tile of one row per strip.  Global accesses
-// are 16-byte vectors, the 8 lanes of a strip covering its line; the 16-byte
-// pieces of a row are permuted by the strip's index so that the 16 lanes that
-// read or write the same piece of their rows fall on distinct banks.
+// LDS of the filter pass per workgroup.
 template <typename TI>
-struct StripStage {
-  typedef typename Vec16<TI>::type VT;
-  static constexpr int V = Vec16<TI>::n;
-  static constexpr int C = 128 / (int)sizeof(TI);    // samples per chunk: a 128-byte line per strip
-  static constexpr int PIECES = C / V;               // 16-byte pieces per row
-  static constexpr int ROWS = 64 / PIECES;           // rows per wave-wide access
-  static constexpr int OPS = PIECES;                 // accesses per tile
-  static constexpr int BYTES = 64 * 128;
-  static __device__ __forceinline__ int slot(int s, int p) { return s * PIECES + (p ^ ((s >> 1) & 7)); }
-};
-
-// Sections up to this many are unrolled, with their states and coefficients
-// in registers; longer cascades keep the states in LDS.
-constexpr int kStripUnroll = 8;
-template <typename TI>
-__host__ __device__ constexpr size_t strip_lds_bytes(int K) {
-  return (size_t)kWavesPerBlock * (StripStage<TI>::BYTES + (K > kStripUnroll ? 1024 * K : 0));
-}
+__host__ __device__ constexpr size_t strip_lds_bytes() { return (size_t)kWavesPerBlock * StripStage<TI>::BYTES; }
 
 // One section on C samples of the lane's strip, in place: the non-recursive
 // stage in descending order, then the recurrence.  t = (b1, b2, a1, a2), b0
@@ -386,42 +434,32 @@ __device__ __forceinline__ void strip_section(double (&X)[C], const double (&t)[
   particular_pass<C, double>(X, t[2], t[3], y0[1], y0[0]);
 }
 
+// One wavefront: the 64 strips from s0.  Every section's state stays in
+// registers, so the sections are unrolled: KT <= 8 is the cascade's own K,
+// with the coefficients in scalar registers too; KT = 16 serves any K up to
+// 16 (a branch per section), with each section's coefficients loaded during
+// the one before it.
 template <typename TI, int KT>
-__global__ __launch_bounds__(kWavesPerBlock * 64) void strip_filter_kernel(const TI *__restrict__ xs,
-                                                                           TI *__restrict__ ys, StripArgs a,
-                                                                           int32_t kmax) {
+__device__ __forceinline__ void strip_filter(const TI *__restrict__ xs, TI *__restrict__ ys, const StripChan &c,
+                                             int64_t s0, unsigned char *lds) {
   typedef StripStage<TI> St;
   typedef typename St::VT VT;
   constexpr int V = St::V, C = St::C;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + w;
-  StripChan c;
-  if (!strip_item(a, item, c)) return;   // uniform per wave
-  const int lane = lane_id();
-  VT *stage = reinterpret_cast<VT *>(smem + (size_t)w * St::BYTES);
-  vd2 *st = reinterpret_cast<vd2 *>(smem + (size_t)kWavesPerBlock * St::BYTES + (size_t)w * 1024 * kmax) + lane;
-  const int64_t s0 = (item - c.first_item) * kStripLanes;
+  constexpr bool FIXED = KT <= 8;
+  const int lane = lane_id(), K = FIXED ? KT : c.K;
+  VT *stage = reinterpret_cast<VT *>(lds);
   const TI *x = xs + c.off;
   TI *y = ys + c.off;
   // the lane's own strip: start state and raw input history
   const int64_t s = s0 + lane, t0 = s * c.len - c.lead - c.shift;
   const bool live = s < c.strips;
-  vd2 ys0[KT > 0 ? KT : 1];   // KT: every section's (y[-2], y[-1]) in registers
+  vd2 ys0[KT];   // every section's (y[-2], y[-1])
   {
     const vd2 *S = reinterpret_cast<const vd2 *>(y + strip_slot<TI>(c, live ? s : 0));
-    if constexpr (KT > 0) {
 #pragma unroll
-      for (int k = 0; k < KT; ++k) {
-        ys0[k] = vd2{0.0, 0.0};
-        if (live && s > 0) ys0[k] = S[k];
-      }
-    } else {
-      for (int k = 0; k < c.K; ++k) {
-        vd2 v = vd2{0.0, 0.0};
-        if (live && s > 0) v = S[k];
-        st[64 * k] = v;
-      }
+    for (int k = 0; k < KT; ++k) {
+      ys0[k] = vd2{0.0, 0.0};
+      if (live && s > 0 && k < K) ys0[k] = S[k];
     }
   }
   double xm2 = (live && t0 >= 2) ? (double)x[t0 - 2] : 0.0;
@@ -440,9 +478,9 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void strip_filter_kernel(const
             16u * (uint32_t)(St::slot(row, lane % St::PIECES) - row * St::PIECES);
   }
   const ctab<double> tab = as_ctab(c.tab);
-  double cf[KT > 0 ? KT : 1][4];   // KT: every section's coefficients in scalar registers
+  double cf[FIXED ? KT : 1][4];
 #pragma unroll
-  for (int k = 0; k < KT; ++k)
+  for (int k = 0; k < (FIXED ? KT : 1); ++k)
 #pragma unroll
     for (int j = 0; j < 4; ++j) cf[k][j] = tab[(int64_t)k * c.stride + OFF_B1 + j];
   const int chunks = (int)(c.len / C);
@@ -490,35 +528,26 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void strip_filter_kernel(const
     double p2 = xm2, p1 = xm1;
     xm2 = X[C - 2];
     xm1 = X[C - 1];
-    if constexpr (KT > 0) {
+    double t[4] = {cf[0][0], cf[0][1], cf[0][2], cf[0][3]};
 #pragma unroll
-      for (int k = 0; k < KT; ++k) {
-        const vd2 y0 = ys0[k];
+    for (int k = 0; k < KT; ++k) {
+      if (!FIXED && k >= K) break;   // uniform
+      const vd2 y0 = ys0[k];
+      if constexpr (FIXED) {
         strip_section<C>(X, cf[k], p2, p1, y0);
-        ys0[k] = vd2{X[C - 2], X[C - 1]};
-        p2 = y0[0];
-        p1 = y0[1];
-      }
-    } else {
-      double t[4] = {tab[OFF_B1], tab[OFF_B2], tab[OFF_A1], tab[OFF_A2]};
-      vd2 y0 = st[0];
-      for (int k = 0; k < c.K; ++k) {
-        // the next section's coefficients and state arrive during this one
-        const int kn = k + 1 < c.K ? k + 1 : 0;
-        const ctab<double> tn = tab + (int64_t)kn * c.stride;
-        const double n0 = tn[OFF_B1], n1 = tn[OFF_B2], n2 = tn[OFF_A1], n3 = tn[OFF_A2];
-        const vd2 ny0 = st[64 * kn];
+      } else {
+        const ctab<double> tn = tab + (int64_t)(k + 1 < K ? k + 1 : 0) * c.stride + OFF_B1;
+        const double n0 = tn[0], n1 = tn[1], n2 = tn[2], n3 = tn[3];
         __builtin_amdgcn_sched_barrier(0);
         strip_section<C>(X, t, p2, p1, y0);
-        st[64 * k] = vd2{X[C - 2], X[C - 1]};
-        p2 = y0[0];
-        p1 = y0[1];
         t[0] = n0;
         t[1] = n1;
         t[2] = n2;
         t[3] = n3;
-        y0 = ny0;
       }
+      ys0[k] = vd2{X[C - 2], X[C - 1]};
+      p2 = y0[0];
+      p1 = y0[1];
     }
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -541,10 +570,14 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void strip_filter_kernel(const
                                              0, 0);
     __builtin_amdgcn_wave_barrier();
   };
-  // the first chunk on its own, so that the loop is entered with the same
-  // accesses in flight as it goes round with
-  chunk(0);
-  for (int ch = 1; ch < chunks; ++ch) chunk(ch);
+  // dropped stores, so that the loop is entered with as many accesses behind
+  // the loads of chunk 1 as it goes round with, and its waits count the same
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < St::OPS; ++j) __builtin_amdgcn_raw_buffer_store_b128(sv4u{0, 0, 0, 0}, ry, 0xfffffe00u + 16 * j, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  int ch = 0;
+  do chunk(ch); while (++ch < chunks);
   if (head >= 0 && lane < V && lane >= c.shift && lane - c.shift < c.n) {
     TI v = firsts[0];
 #pragma unroll
@@ -552,6 +585,42 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void strip_filter_kernel(const
       if (lane == i) v = firsts[i];
     y[lane - c.shift] = v;
   }
+}
+
+// Single signals: the cascade's own instance.
+template <typename TI, int KT>
+__global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_filter_kernel(const TI *__restrict__ xs,
+                                                                              TI *__restrict__ ys, StripArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + w;
+  StripChan c;
+  if (!strip_item(a, item, c)) return;   // uniform per wave
+  strip_filter<TI, KT>(xs, ys, c, (item - c.first_item) * kStripLanes, smem + (size_t)w * StripStage<TI>::BYTES);
+}
+
+// Batches: the workgroups before `rows_blocks` filter the channels that stay
+// with the tiles (their serial chains start first and finish beside the
+// strips), the others 64 strips per wavefront.  Where the batch's present
+// channels have no strips (a replan), every workgroup takes tiles.
+template <int N, typename TI>
+__global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_batched_kernel(
+    const TI *__restrict__ xs, TI *__restrict__ ys, const BatchChan *__restrict__ chans,
+    const int32_t *__restrict__ item_chan, const int64_t *__restrict__ hdr, int32_t kmax, int32_t rows_blocks,
+    StripArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const bool strips = as_ctab(a.items_live)[0] > 0;
+  if (!strips || (int)blockIdx.x < rows_blocks) {
+    const int64_t step = (int64_t)(strips ? rows_blocks : (int)gridDim.x) * kWavesPerBlock;
+    for (int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + w; item < hdr[0]; item += step)
+      batched_rows<N, TI, double, true, SOS_PH, kL>(xs, ys, chans, item_chan, item, kmax, smem);
+    return;
+  }
+  const int64_t item = (int64_t)((int)blockIdx.x - rows_blocks) * kWavesPerBlock + w;
+  StripChan c;
+  if (!strip_item(a, item, c)) return;   // uniform per wave
+  strip_filter<TI, 16>(xs, ys, c, (item - c.first_item) * kStripLanes, smem + (size_t)w * StripStage<TI>::BYTES);
 }
 
 }  // namespace sosf

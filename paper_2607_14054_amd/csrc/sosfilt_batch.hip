@@ -248,6 +248,7 @@ sos_status schedule(sos_batch_s &b, const sos_plan_t *plans, int32_t C, const in
     for (int64_t q = 0; q < quads[c]; ++q) b.item_chan.push_back(i);
     b.items += quads[c];
   }
+  b.rows_items = b.items;
   b.adj = false;
   if (!b.host_only) return schedule_batch_adjoint(b, plans, tile_groups);
   return SOS_OK;
@@ -258,17 +259,19 @@ sos_status schedule(sos_batch_s &b, const sos_plan_t *plans, int32_t C, const in
 // channels, adjoint items, gsos rows.  The regions are sized by the batch's
 // room, fixed at creation.
 struct BlobLayout {
-  size_t hdr, chans, items, adj, adj_items, red, bytes;
+  size_t hdr, chans, items, strips, strip_items, adj, adj_items, red, bytes;
 };
 
 size_t up16(size_t v) { return (v + 15) & ~(size_t)15; }
 
-BlobLayout blob_layout(size_t C, size_t items, size_t adj_items, size_t rows) {
+BlobLayout blob_layout(size_t C, size_t items, size_t strip_items, size_t adj_items, size_t rows) {
   BlobLayout l;
   l.hdr = 0;
-  l.chans = 16;
+  l.chans = 32;
   l.items = up16(l.chans + C * sizeof(BatchChan));
-  l.adj = up16(l.items + items * sizeof(int32_t));
+  l.strips = up16(l.items + items * sizeof(int32_t));
+  l.strip_items = up16(l.strips + (strip_items ? C : 0) * sizeof(StripChan));
+  l.adj = up16(l.strip_items + strip_items * sizeof(int32_t));
   l.adj_items = up16(l.adj + C * sizeof(AdjChan));
   l.red = up16(l.adj_items + adj_items * sizeof(int32_t));
   l.bytes = up16(l.red + rows * sizeof(int32_t));
@@ -277,14 +280,19 @@ BlobLayout blob_layout(size_t C, size_t items, size_t adj_items, size_t rows) {
 
 // The layout of the batch's room.
 BlobLayout blob_layout(const sos_batch_s &b) {
-  return blob_layout((size_t)b.C_cap, (size_t)b.items_cap, (size_t)b.adj_items_cap, (size_t)b.rows_cap);
+  return blob_layout((size_t)b.C_cap, (size_t)b.items_cap, (size_t)b.strip_cap, (size_t)b.adj_items_cap,
+                     (size_t)b.rows_cap);
 }
 
 void pack(const sos_batch_s &b, const BlobLayout &l, unsigned char *dst) {
-  const int64_t hdr[2] = {b.items, b.gen};
+  const int64_t hdr[4] = {b.rows_items, b.gen, b.strip_items, 0};
   std::memcpy(dst + l.hdr, hdr, sizeof(hdr));
   std::memcpy(dst + l.chans, b.chans.data(), b.chans.size() * sizeof(BatchChan));
   std::memcpy(dst + l.items, b.item_chan.data(), b.item_chan.size() * sizeof(int32_t));
+  if (b.strip_items > 0) {
+    std::memcpy(dst + l.strips, b.strip_chans.data(), b.strip_chans.size() * sizeof(StripChan));
+    std::memcpy(dst + l.strip_items, b.strip_item_chan.data(), b.strip_item_chan.size() * sizeof(int32_t));
+  }
   if (b.adj) {
     std::memcpy(dst + l.adj, b.adj_chans.data(), b.adj_chans.size() * sizeof(AdjChan));
     std::memcpy(dst + l.adj_items, b.adj_item_chan.data(), b.adj_item_chan.size() * sizeof(int32_t));
@@ -297,6 +305,8 @@ void point(sos_batch_s &b, const BlobLayout &l) {
     b.d_hdr = nullptr;
     b.d_chans = nullptr;
     b.d_item_chan = nullptr;
+    b.d_strips = nullptr;
+    b.d_strip_item = nullptr;
     b.d_adj = nullptr;
     b.d_adj_item = nullptr;
     b.d_adj_red = nullptr;
@@ -305,6 +315,8 @@ void point(sos_batch_s &b, const BlobLayout &l) {
   b.d_hdr = reinterpret_cast<const int64_t *>(b.d_blob + l.hdr);
   b.d_chans = reinterpret_cast<BatchChan *>(b.d_blob + l.chans);
   b.d_item_chan = reinterpret_cast<int32_t *>(b.d_blob + l.items);
+  b.d_strips = reinterpret_cast<StripChan *>(b.d_blob + l.strips);
+  b.d_strip_item = reinterpret_cast<int32_t *>(b.d_blob + l.strip_items);
   b.d_adj = reinterpret_cast<AdjChan *>(b.d_blob + l.adj);
   b.d_adj_item = reinterpret_cast<int32_t *>(b.d_blob + l.adj_items);
   b.d_adj_red = reinterpret_cast<int32_t *>(b.d_blob + l.red);
@@ -333,6 +345,7 @@ sos_status fits(const sos_batch_s &b, const sos_batch_s &t) {
   if (b.inst_b0one && !t.b0one) return SOS_E_UNSUPPORTED;
   if (b.inst_mix != SOS_AUTO && t.mix != b.inst_mix) return SOS_E_UNSUPPORTED;
   if (t.C > b.C_cap || t.items > b.items_cap || t.kmax > b.kmax_cap) return SOS_E_NOMEM;
+  if (t.strip_items > b.strip_cap || (t.strip_scan && !b.strip_scan_cap)) return SOS_E_NOMEM;
   if (t.adj != b.adj) return SOS_E_UNSUPPORTED;
   if (t.adj && ((int64_t)t.adj_item_chan.size() > b.adj_items_cap || (int64_t)t.adj_red.size() > b.rows_cap))
     return SOS_E_NOMEM;
@@ -349,7 +362,8 @@ bool batch_descriptors_valid(const sos_batch_s &b) {
     const unsigned char *q = static_cast<const unsigned char *>(p);
     return q >= b.d_blob && q < b.d_blob + b.blob_cap;
   };
-  return inside(b.d_hdr) && inside(b.d_chans) && inside(b.d_item_chan) && inside(b.d_adj) && inside(b.d_adj_item) &&
+  return inside(b.d_hdr) && inside(b.d_chans) && inside(b.d_item_chan) && inside(b.d_strips) &&
+         (b.strip_cap == 0 || inside(b.d_strip_item)) && inside(b.d_adj) && inside(b.d_adj_item) &&
          inside(b.d_adj_red);
 }
 
@@ -393,6 +407,12 @@ sos_status sos_batch_plan(const sos_plan_t *plans, int32_t C, const int64_t *n,
     b->rows_cap = b->adj ? (int64_t)b->adj_red.size() : 0;
     b->inst_b0one = b->b0one;
     b->inst_mix = b->mix;
+    // long channels by strips (a batch with a reservation keeps the one
+    // launch that serves every later set)
+    if (!host_only) strip_schedule(*b, plans);
+    b->strip_cap = b->strip_items;
+    b->strip_rows_cap = b->rows_items;
+    b->strip_scan_cap = b->strip_scan;
   }
   if (!host_only) {
     const BlobLayout l = blob_layout(*b);
@@ -448,6 +468,11 @@ sos_status sos_batch_replan(sos_batch_t b, const sos_plan_t *plans, int32_t C, c
   // a device batch keeps its room and its launch; a host-only batch is only
   // a schedule, and takes the new set's
   if (!b->host_only) {
+    // strips where the launch has them and the set fits its strip items
+    if (b->strip_cap > 0) {
+      strip_schedule(t, plans);
+      if (fits(*b, t) != SOS_OK) strip_unschedule(t);
+    }
     st = fits(*b, t);
     if (st != SOS_OK) return st;
   }
@@ -465,6 +490,7 @@ sos_status sos_batch_replan(sos_batch_t b, const sos_plan_t *plans, int32_t C, c
     t.items_cap = t.items;
     t.adj_items_cap = 0;
     t.rows_cap = 0;
+    t.strip_cap = 0;
     t.inst_b0one = t.b0one;
     t.inst_mix = t.mix;
   } else {
@@ -473,6 +499,9 @@ sos_status sos_batch_replan(sos_batch_t b, const sos_plan_t *plans, int32_t C, c
     t.items_cap = b->items_cap;
     t.adj_items_cap = b->adj_items_cap;
     t.rows_cap = b->rows_cap;
+    t.strip_cap = b->strip_cap;
+    t.strip_rows_cap = b->strip_rows_cap;
+    t.strip_scan_cap = b->strip_scan_cap;
     t.inst_b0one = b->inst_b0one;
     t.inst_mix = b->inst_mix;
   }
@@ -526,6 +555,7 @@ sos_status sos_filt_batched(sos_batch_t b, const void *x, void *y, void *workspa
   if ((xb | yb) & 15) return SOS_E_ARG;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if (b->block) return launch_block_batched(*b, x, y, s);
+  if (b->strip_cap > 0) return launch_strip_batched(*b, x, y, s);
   return dispatch_rows_l<LaunchBatched>(b->N, b->L, b->io_dtype, b->compute_dtype, b->inst_b0one, b->inst_mix, *b,
                                         x, y, s);
 }

@@ -2,8 +2,10 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <numeric>
 #include <vector>
 
+#include "batch.hpp"
 #include "dispatch.hpp"
 #include "kernels_strip.hpp"
 #include "plan.hpp"
@@ -18,13 +20,51 @@ bool strip_supported(const sos_plan_s &p) {
          !(p.flags & (SOS_FLAG_CARRY_SCAN | SOS_FLAG_CARRY_RUNIN));
 }
 
+namespace {
+
+// phi_pow again, each power the square of the one before in extended
+// precision, rounded to FP64 at the end.  A section's state depends on its
+// own and on those of the sections before it, so the matrices are block lower
+// triangular and a product needs only the blocks on and below the diagonal.
+void square_powers(sos_plan_s &p) {
+  const int D = 2 * p.K;
+  std::vector<long double> a(p.phi.begin(), p.phi.end()), b((size_t)D * D);
+  // the one-step transition's last row of each section, from the coefficients
+  // (its entries are short sums that FP64 rounds)
+  for (int col = 0; col < D; ++col) {
+    long double in2 = 0.0L, in1 = 0.0L, now = 0.0L;
+    for (int k = 0; k < p.K; ++k) {
+      const double *o = &p.rows[5 * k];
+      const long double y2 = col == 2 * k ? 1.0L : 0.0L, y1 = col == 2 * k + 1 ? 1.0L : 0.0L;
+      const long double yn = o[0] * now + o[1] * in1 + o[2] * in2 - o[3] * y1 - o[4] * y2;
+      a[(size_t)(2 * k + 1) * D + col] = yn;
+      in2 = y2;
+      in1 = y1;
+      now = yn;
+    }
+  }
+  for (size_t q = 1; q < p.phi_pow.size(); ++q) {
+    std::fill(b.begin(), b.end(), 0.0L);
+    for (int i = 0; i < D; ++i)
+      for (int k = 0; k < (i | 1) + 1; ++k) {
+        const long double v = a[(size_t)i * D + k];
+        for (int j = 0; j < (k | 1) + 1; ++j) b[(size_t)i * D + j] += v * a[(size_t)k * D + j];
+      }
+    a.swap(b);
+    for (int i = 0; i < D * D; ++i) p.phi_pow[q][i] = (double)a[i];
+  }
+}
+
+}  // namespace
+
 // Device tables: the state table, the all-pole responses and the padded
 // powers of the transition.
 //   state table: entry (row i, j) is the response of state value i at a
 //     strip's end to the raw input j samples before the end, h_k[j - d] with
 //     k = i / 2 and d = 1 for even rows (y[-2]), 0 for odd ones (y[-1]);
-//     block b, row i, element e holds j = 16 b + 15 - e (ascending time), so
-//     that a lane's four MFMA A operands are consecutive;
+//     element e (ascending time) of block b holds j = 16 b + 15 - e; in the
+//     order the products read them, [block][row tile][pair][lane][2], lane
+//     (i, q) of pair k holding row i, elements 4 q + 2 k and the next;
 //   all-pole responses g_k: section k's output to a unit input of the first
 //     section's recursive part (h_k = g_k + b1 g_k[. - 1] + b2 g_k[. - 2]).
 sos_status upload_strip(sos_plan_s &p) {
@@ -62,17 +102,24 @@ sos_status upload_strip(sos_plan_s &p) {
     if (span > 1) h[2] = gk[1] + b1 * gk[0];
     for (int l = 2; l < span; ++l) h[l + 1] = gk[l] + b1 * gk[l - 1] + b2 * gk[l - 2];
     for (int b = 0; b < span / 16; ++b) {
-      double *even = &t[((size_t)b * R + 2 * k) * 16], *odd = even + 16;
       const double *hb = &h[16 * b];
+      const int i = (2 * k) % 16;
       for (int e = 0; e < 16; ++e) {
-        even[e] = hb[15 - e];   // d = 1: h_k[j - 1]
-        odd[e] = hb[16 - e];    // d = 0: h_k[j]
+        double *at = &t[(size_t)b * (16 * R) + (((2 * k) / 16 * 2 + e % 4 / 2) * 64 + e / 4 * 16 + i) * 2 + e % 2];
+        at[0] = hb[15 - e];   // d = 1: h_k[j - 1]
+        at[2] = hb[16 - e];   // d = 0: h_k[j]
       }
     }
   }
+  // FP64 I/O: the powers squared in extended precision.  Repeated FP64
+  // squaring loses digits that the states then carry through the signal
+  // (K = 16, r = 0.99 .. 0.999: results 1.1e-12 off with FP64 powers, 1.4e-13
+  // with these, the plain recurrence 6e-14).
+  if (p.io_dtype == SOS_F64) square_powers(p);
   for (size_t q = 0; q < p.phi_pow.size(); ++q)
     for (int i = 0; i < D; ++i)
-      for (int j = 0; j < D; ++j) ph[q * R * R + (size_t)i * R + j] = p.phi_pow[q][(size_t)i * D + j];
+      for (int j = 0; j < D; ++j)   // the A operand's order: [row tile][step][lane]
+        ph[q * R * R + (size_t)(i / 16 * 4 * mt + j / 4) * 64 + j % 4 * 16 + i % 16] = p.phi_pow[q][(size_t)i * D + j];
   if (hipMalloc(&p.d_strip, t.size() * sizeof(double)) != hipSuccess) {
     p.d_strip = nullptr;
     return SOS_E_NOMEM;
@@ -175,8 +222,7 @@ sos_status launch(const StripArgs &a, int64_t items, int terms, int K, const voi
   if (terms > 16)
     hipLaunchKernelGGL((strip_scan_kernel<TI, MT>), dim3((unsigned)items), dim3(256), 0, s, yi, a);
 #define SOSF_STRIP_FILTER(KT)                                                                             \
-  hipLaunchKernelGGL((strip_filter_kernel<TI, KT>), dim3(blocks), dim3(256), strip_lds_bytes<TI>(K), s, xi, yi, a, \
-                     (int32_t)K)
+  hipLaunchKernelGGL((strip_filter_kernel<TI, KT>), dim3(blocks), dim3(256), strip_lds_bytes<TI>(), s, xi, yi, a)
   switch (K) {
     case 1: SOSF_STRIP_FILTER(1); break;
     case 2: SOSF_STRIP_FILTER(2); break;
@@ -186,7 +232,7 @@ sos_status launch(const StripArgs &a, int64_t items, int terms, int K, const voi
     case 6: SOSF_STRIP_FILTER(6); break;
     case 7: SOSF_STRIP_FILTER(7); break;
     case 8: SOSF_STRIP_FILTER(8); break;
-    default: SOSF_STRIP_FILTER(0); break;
+    default: SOSF_STRIP_FILTER(16); break;
   }
 #undef SOSF_STRIP_FILTER
   return hipGetLastError() == hipSuccess ? SOS_OK : SOS_E_DEVICE;
@@ -201,6 +247,136 @@ sos_status launch_strip(const sos_plan_s &p, const StripChan &c, const void *x, 
   if (p.io_dtype == SOS_F32)
     return c.mt == 1 ? launch<float, 1>(a, a.items, c.terms, p.K, x, y, s) : launch<float, 2>(a, a.items, c.terms, p.K, x, y, s);
   return c.mt == 1 ? launch<double, 1>(a, a.items, c.terms, p.K, x, y, s) : launch<double, 2>(a, a.items, c.terms, p.K, x, y, s);
+}
+
+// Strips in a batch, where the tiles would spend much of their work on
+// run-ins: 64 channels x 2^20 with poles up to r = 0.999 (FP32, K = 8) take
+// 382 us by tiles and 203 by strips, while a ragged batch with short run-ins
+// (256 channels of 2^10 .. 2^22, K = 1 .. 16, r <= 0.95) is better off with
+// the tiles (438 us against 520).  The line is 1.5 times the channels' own
+// section-samples.  A wavefront of 64 strips costs about (K + 5) len (a chunk
+// that filters nothing takes as long as five sections); the lengths share the
+// long channels' work out to two wavefronts per SIMD.  Channels too short for
+// 64 strips of a sensible length stay with the tiles.
+void strip_schedule(sos_batch_s &b, const sos_plan_t *plans) {
+  strip_unschedule(b);
+  if (b.block || b.host_only || !b.b0one || b.mix != SOS_PH || b.tile_groups > 0) return;
+  constexpr int64_t kLeast = 16384, kLeastTotal = 1 << 22;
+  constexpr double kBase = 5.0, kRunIn = 1.5;
+  double work = 0.0, own = 0.0, tiles = 0.0;
+  int64_t total = 0;
+  std::vector<char> takes(b.C, 0);
+  for (int i = 0; i < b.C; ++i) {
+    const int c = b.order[i];
+    takes[c] = plans[c]->d_strip && b.n[c] >= kLeast;
+    if (!takes[c]) continue;
+    const int64_t items = (i + 1 < b.C ? b.chans[i + 1].first_item : b.items) - b.chans[i].first_item;
+    const int64_t warm = std::min<int64_t>(b.chans[i].warm, (b.n[c] - 1) / b.tile[c] * b.tile[c]);
+    tiles += (double)items * (64 / b.L) * plans[c]->K * (double)(b.tile[c] + warm);
+    own += (double)b.n[c] * plans[c]->K;
+    work += (double)b.n[c] * (plans[c]->K + kBase);
+    total += b.n[c];
+  }
+  if (total < kLeastTotal || tiles < kRunIn * own) return;
+  const double quota = work / (2.0 * plans[0]->simds * kStripLanes);   // a lane's share
+  const int64_t V = b.io_dtype == SOS_F64 ? 2 : 4;
+  std::vector<StripChan> chans;
+  std::vector<double> cost;
+  for (int c = 0; c < b.C; ++c) {
+    if (!takes[c]) continue;
+    const int64_t n = b.n[c], want = std::max<int64_t>((int64_t)(quota / (plans[c]->K + kBase)), 64);
+    const int64_t w = std::max<int64_t>((n + 64 * want / 2) / (64 * want), 1);   // wavefronts of the channel
+    StripChan s{};
+    if (!strip_geometry(*plans[c], n, (int32_t)(b.off[c] % V), (n + 64 * w - 1) / (64 * w), s)) {
+      takes[c] = 0;
+      continue;
+    }
+    s.off = b.off[c];
+    chans.push_back(s);
+    cost.push_back((s.K + kBase) * (double)s.len);
+  }
+  if (chans.empty()) return;
+  // costliest wavefronts first
+  std::vector<int32_t> order(chans.size());
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int32_t i, int32_t j) { return cost[i] > cost[j]; });
+  for (int32_t i : order) {
+    StripChan s = chans[i];
+    s.first_item = b.strip_items;
+    const int64_t items = (s.strips + kStripLanes - 1) / kStripLanes;
+    b.strip_item_chan.insert(b.strip_item_chan.end(), (size_t)items, (int32_t)b.strip_chans.size());
+    b.strip_items += items;
+    b.strip_scan = b.strip_scan || s.terms > 16;
+    b.strip_chans.push_back(s);
+  }
+  // the tiles keep the other channels' items
+  std::vector<int32_t> keep;
+  for (int i = 0; i < b.C; ++i) {
+    BatchChan &ch = b.chans[i];
+    const int64_t first = ch.first_item, end = i + 1 < b.C ? b.chans[i + 1].first_item : b.items;
+    ch.first_item = (int64_t)keep.size();
+    if (!takes[b.order[i]]) keep.insert(keep.end(), (size_t)(end - first), i);
+  }
+  b.item_chan.swap(keep);
+  b.rows_items = (int64_t)b.item_chan.size();
+}
+
+// Every channel back to the tiles.
+void strip_unschedule(sos_batch_s &b) {
+  if (b.strip_items == 0) return;
+  b.strip_items = 0;
+  b.strip_scan = false;
+  b.strip_chans.clear();
+  b.strip_item_chan.clear();
+  b.item_chan.clear();
+  const int64_t G = (int64_t)b.N * b.L, R = 64 / b.L;
+  for (int i = 0; i < b.C; ++i) {
+    BatchChan &ch = b.chans[i];
+    ch.first_item = (int64_t)b.item_chan.size();
+    const int64_t groups = ch.n ? (ch.n + ch.shift + G - 1) / G : 0, tg = ch.tile / G;
+    b.item_chan.insert(b.item_chan.end(), (size_t)((groups + R * tg - 1) / (R * tg)), i);
+  }
+  b.rows_items = (int64_t)b.item_chan.size();
+}
+
+namespace {
+
+template <typename TI, int N>
+sos_status launch_batched(const sos_batch_s &b, const void *x, void *y, hipStream_t s) {
+  const TI *xi = static_cast<const TI *>(x);
+  TI *yi = static_cast<TI *>(y);
+  StripArgs a{};
+  a.chans = b.d_strips;
+  a.item_chan = b.d_strip_item;
+  a.items_live = b.d_hdr + 2;
+  const unsigned blocks = (unsigned)((b.strip_cap + kWavesPerBlock - 1) / kWavesPerBlock);
+  const unsigned rows = (unsigned)((b.strip_rows_cap + kWavesPerBlock - 1) / kWavesPerBlock);
+  hipLaunchKernelGGL((strip_state_batched_kernel<TI>), dim3(blocks), dim3(256), 0, s, xi, yi, a);
+  if (b.strip_scan_cap) {
+    hipLaunchKernelGGL((strip_scan_kernel<TI, 1>), dim3((unsigned)b.strip_cap), dim3(256), 0, s, yi, a);
+    hipLaunchKernelGGL((strip_scan_kernel<TI, 2>), dim3((unsigned)b.strip_cap), dim3(256), 0, s, yi, a);
+  }
+  const size_t lds = std::max(strip_lds_bytes<TI>(), (size_t)lds_bytes<N, TI, double, kL>(b.kmax_cap));
+  hipLaunchKernelGGL((strip_batched_kernel<N, TI>), dim3(rows + blocks), dim3(256), lds, s, xi, yi, b.d_chans,
+                     b.d_item_chan, b.d_hdr, (int32_t)b.kmax_cap, (int32_t)rows, a);
+  return hipGetLastError() == hipSuccess ? SOS_OK : SOS_E_DEVICE;
+}
+
+template <typename TI>
+sos_status launch_batched_n(const sos_batch_s &b, const void *x, void *y, hipStream_t s) {
+  switch (b.N) {
+    case 8: return launch_batched<TI, 8>(b, x, y, s);
+    case 16: return launch_batched<TI, 16>(b, x, y, s);
+    case 32: return launch_batched<TI, 32>(b, x, y, s);
+    case 64: return launch_batched<TI, 64>(b, x, y, s);
+    default: return SOS_E_UNSUPPORTED;
+  }
+}
+
+}  // namespace
+
+sos_status launch_strip_batched(const sos_batch_s &b, const void *x, void *y, hipStream_t s) {
+  return b.io_dtype == SOS_F32 ? launch_batched_n<float>(b, x, y, s) : launch_batched_n<double>(b, x, y, s);
 }
 
 }  // namespace sosf

@@ -20,9 +20,9 @@ constexpr int kStripLanes = 64;          // strips per wavefront of the filter k
 // strip long enough for its start state.
 struct StripChan {
   const double *tab;       // the plan's section rows
-  const double *hop;       // state table, [block][row][16]: see build_strip_tables
+  const double *hop;       // state table, in the order the products read it (upload_strip)
   const double *g;         // all-pole responses, [K][gstride]
-  const double *phi;       // padded powers Phi^(2^j), [j][16 MT][16 MT]
+  const double *phi;       // padded powers Phi^(2^j) in the A operand's order
   int64_t off, n;          // first sample in x / y, length
   int64_t len, strips;     // samples per strip (a multiple of 32; a power of two where terms > 1), strips
   int64_t first_item;      // first work item (64 strips) of the channel

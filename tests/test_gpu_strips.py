@@ -117,3 +117,77 @@ def test_strips_graph_replays_match_eager():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(yout, ref)
+
+
+def _batch(lengths, Ks, offsets, r, seed, io, N):
+    sos = [W.make_sos(k, r[0], r[1], seed + c) for c, k in enumerate(Ks)]
+    plans = [S.Plan(s, io_dtype=io, N=N) for s in sos]
+    return sos, plans, list(lengths), list(offsets)
+
+
+def _check_batch(yb, xb, sos, lengths, offsets, io, plans=None):
+    """Strips at the bar of the FP64 paths; channels below 16384 samples stay
+    with the tiles, whose FP64 scans are 6.5e-11 off for K = 16 at r > 0.99:
+    they are held to twice the error of the tiles' single-signal call."""
+    gap = np.ones(len(xb), bool)
+    for c, (s, n, o) in enumerate(zip(sos, lengths, offsets)):
+        gap[o:o + n] = False
+        ref = oracle.sosfilt(xb[o:o + n], s)
+        if io == "f32":
+            assert oracle.rel_rms(yb[o:o + n], ref) < 1e-6
+        else:
+            ld = oracle.sosfilt_ld(xb[o:o + n], s)
+            bar = max(1e-12, 4 * oracle.rel_rms(ref, ld))
+            if n < 16384:
+                one = S.filt(plans[c], torch.from_numpy(xb[o:o + n].copy()).to(DEV)).cpu().numpy()
+                bar = max(bar, 2 * oracle.rel_rms(one, ld))
+            assert oracle.rel_rms(yb[o:o + n], ld) <= bar
+    assert (yb[gap] == 7.0).all()
+
+
+@pytest.mark.parametrize("io", ["f32", "f64"])
+def test_strips_in_a_batch(io):
+    """Run-ins long against the channels: long channels by strips (starts on
+    and off 16-byte boundaries, K on both sides of 8), short ones by tiles in
+    the same launch; the samples between channels stay."""
+    lengths = [2000001, 16384, 5000, 1200007, 300, 700000, 65537, 1 << 20]
+    Ks = [8, 3, 16, 1, 5, 16, 9, 2]
+    offsets, at = [], 0
+    for c, n in enumerate(lengths):
+        at += (0, 1, 3, 2, 7, 5, 0, 6)[c]
+        offsets.append(at)
+        at += n
+    dt = np.float32 if io == "f32" else np.float64
+    sos, plans, lengths, offsets = _batch(lengths, Ks, offsets, (0.99, 0.999), 960, io, 32)
+    b = S.Batch(plans, lengths, offsets)
+    xb = W.make_signal(b.total + 9, 961, dt)
+    y = torch.full((len(xb),), 7.0, dtype=torch.float32 if io == "f32" else torch.float64, device=DEV)
+    S.filt_batched(b, torch.from_numpy(xb).to(DEV), y)
+    torch.cuda.synchronize()
+    _check_batch(y.cpu().numpy(), xb, sos, lengths, offsets, io, plans)
+
+
+def test_strips_batch_graph_and_replans():
+    """A captured launch of a batch with strips replays after replans (that fit its room), to
+    channels that all take the tiles and back; so do eager launches."""
+    big = _batch([1 << 21, 1 << 21, 300001], [8, 8, 4], [0, 1 << 21, (1 << 22) + 1], (0.99, 0.999), 970, "f32", 32)
+    small = _batch([4000, 10000, 12000], [2, 8, 3], [5, 5000, 200000], (0.5, 0.9), 980, "f32", 32)
+    b = S.Batch(big[1], big[2], big[3])
+    stream = torch.cuda.Stream()
+    xb = W.make_signal((1 << 22) + 300100, 971, np.float32)
+    x = torch.from_numpy(xb).to(DEV)
+    y = torch.full_like(x, 7.0)
+    torch.cuda.synchronize()
+    S.filt_batched(b, x, y, stream)
+    stream.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        S.filt_batched(b, x, y, stream)
+    for sos, plans, lengths, offsets in (big, small, big, small):
+        b.replan(plans, lengths, offsets, stream)
+        for launch in (g.replay, lambda: S.filt_batched(b, x, y, stream)):
+            with torch.cuda.stream(stream):
+                y.fill_(7.0)
+                launch()
+            stream.synchronize()
+            _check_batch(y.cpu().numpy(), xb, sos, lengths, offsets, "f32")
