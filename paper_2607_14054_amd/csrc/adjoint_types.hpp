@@ -8,6 +8,10 @@
 
 namespace sosf {
 
+// Adjoint rows per section (kBwdRow doubles): b0 b1 b2 a1 a2 (divided by a0,
+// b0 not factored), the forward pass's cumulative b0 scale, the caller's a0.
+enum : int { BW_B0 = 0, BW_B1 = 1, BW_B2 = 2, BW_A1 = 3, BW_A2 = 4, BW_SCALE = 5, BW_A0 = 6 };
+
 // Recompute mode: where a group's section inputs u_k come from.  For
 // K >= 8 the forward pass keeps, besides the group's checkpoint, the input
 // u_H of section H = K / 2 in the workspace (8 bytes per sample, which

@@ -45,6 +45,12 @@ struct sos_batch_s {
   std::vector<sosf::AdjChan> adj_chans;   // in launch order
   std::vector<int32_t> adj_item_chan;     // item -> index into adj_chans
   std::vector<int32_t> adj_red;           // gsos row -> index into adj_chans
+  // every channel's adjoint by strips (kernels_strip_adjoint.hpp): its work
+  // items, then the entries of adj_item_chan (0: the tile kernels)
+  int64_t adj_strip_items = 0;
+  int64_t adj_strip_room = INT64_MAX;       // a replan's: more items than these stay with the tiles
+  std::vector<sosf::AdjStrip> adj_strips;   // in launch order
+  sosf::AdjStrip *d_adj_strips = nullptr;
   sosf::AdjChan *d_adj = nullptr;
   int32_t *d_adj_item = nullptr;
   int32_t *d_adj_red = nullptr;
@@ -78,6 +84,11 @@ namespace sosf {
 void strip_schedule(sos_batch_s &b, const sos_plan_t *plans);
 void strip_unschedule(sos_batch_s &b);
 sos_status launch_strip_batched(const sos_batch_s &b, const void *x, void *y, hipStream_t s);
+// the adjoint by strips (sosfilt_strip_adjoint.hip): moves a scheduled
+// adjoint to the strips where it gains; the launches
+void adj_strip_schedule(sos_batch_s &b, const sos_plan_t *plans);
+sos_status launch_adj_strip_batched(bool forward, bool adjoint, const sos_batch_s &b, const void *x, void *y,
+                                    const void *gy, void *gx, double *ws, hipStream_t s);
 // the adjoint schedule, host side (sosfilt_backward.hip)
 sos_status schedule_batch_adjoint(sos_batch_s &b, const sos_plan_t *plans, int32_t tile_groups);
 // batched block filtering (sosfilt_block.hip)

@@ -143,10 +143,6 @@ __device__ __forceinline__ void allpole_ph(double (&X)[N], ctab<double> c, doubl
   ys[1] = last_of_row(q);
 }
 
-// Adjoint rows per section (kBwdRow doubles): b0 b1 b2 a1 a2 (divided by a0,
-// b0 not factored), the forward pass's cumulative b0 scale, the caller's a0.
-enum : int { BW_B0 = 0, BW_B1 = 1, BW_B2 = 2, BW_A1 = 3, BW_A2 = 4, BW_SCALE = 5, BW_A0 = 6 };
-
 struct BwdArgs {
   int64_t n, np;            // samples; n rounded up to the vector width
   int64_t tile, warm, ntiles;

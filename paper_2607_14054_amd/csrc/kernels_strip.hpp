@@ -37,18 +37,23 @@ struct StripArgs {
   StripChan one;                 // single signal
 };
 
+// A descriptor, through the constant address space, so that its fields arrive
+// in scalar registers.
+template <typename T>
+__device__ __forceinline__ void load_desc(T &d, const T *src) {
+  const ctab<uint64_t> p = as_ctab(reinterpret_cast<const uint64_t *>(src));
+  uint64_t raw[sizeof(T) / 8];
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 8); ++i) raw[i] = p[i];
+  __builtin_memcpy(&d, raw, sizeof(d));
+}
+
 // The channel and the strip range of a work item (64 strips); false past the
 // last item (uniform per wave).
 __device__ __forceinline__ bool strip_item(const StripArgs &a, int64_t item, StripChan &c) {
   if (a.chans) {
     if (item >= as_ctab(a.items_live)[0]) return false;
-    // (through the constant address space, so that the fields arrive in
-    // scalar registers)
-    const ctab<uint64_t> p = as_ctab(reinterpret_cast<const uint64_t *>(a.chans + as_ctab(a.item_chan)[item]));
-    uint64_t raw[sizeof(StripChan) / 8];
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(StripChan) / 8); ++i) raw[i] = p[i];
-    __builtin_memcpy(&c, raw, sizeof(c));
+    load_desc(c, a.chans + as_ctab(a.item_chan)[item]);
   } else {
     if (item >= a.items) return false;
     c = a.one;
@@ -100,7 +105,7 @@ struct StripStage {
   static __device__ __forceinline__ int slot(int s, int p) { return s * PIECES + (p ^ ((s >> 1) & 7)); }
 };
 
-// Rotates a value d lanes up inside its 16-lane row (d = 1, 2, 4, 8).
+// Rotates a value d lanes up inside its 16-lane row (d = 1 .. 15).
 template <int D>
 __device__ __forceinline__ double row_ror(double v) {
   const uint64_t b = (uint64_t)__double_as_longlong(v);
@@ -111,8 +116,8 @@ __device__ __forceinline__ double row_ror(double v) {
 
 // One doubling round over the wavefront's strips: v_s += P v_{s-D}, P the
 // transition over D strips (A operand layout).  Strips before the first tile
-// count as zero.
-template <int D, int NT, int MT>
+// count as zero.  REV: v_s += P v_{s+D}, zero past the last tile.
+template <int D, int NT, int MT, bool REV>
 __device__ __forceinline__ void strip_round(sv4d (&v)[NT][MT], const double (&P)[MT][4 * MT], int i) {
   double sh[NT][MT][4];
 #pragma unroll
@@ -121,8 +126,11 @@ __device__ __forceinline__ void strip_round(sv4d (&v)[NT][MT], const double (&P)
     for (int m = 0; m < MT; ++m)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const double cur = row_ror<D>(v[t][m][r]), prev = t > 0 ? row_ror<D>(v[t > 0 ? t - 1 : 0][m][r]) : 0.0;
-        sh[t][m][r] = i < D ? prev : cur;
+        constexpr int ROT = REV ? 16 - D : D;
+        const int u = REV ? t + 1 : t - 1;   // the tile that shifts in
+        const bool in = REV ? u < NT : u >= 0;
+        const double cur = row_ror<ROT>(v[t][m][r]), next = in ? row_ror<ROT>(v[in ? u : t][m][r]) : 0.0;
+        sh[t][m][r] = (REV ? i >= 16 - D : i < D) ? next : cur;
       }
 #pragma unroll
   for (int k = 0; k < 4 * MT; ++k)
@@ -143,6 +151,64 @@ __device__ __forceinline__ void strip_power(double (&P)[MT][4 * MT], const doubl
     for (int k = 0; k < 4 * MT; ++k) P[m][k] = f[(m * 4 * MT + k) * 64];
 }
 
+// P[j] = Phi^(len 2^j), j < 4, of a 16-row state for any len: the product of
+// the powers in len's bits, then squares.  D's layout of F^T G^T is the A
+// operand's of G F, and the A operand's layout of M is the B operand's of M^T,
+// so both P (M) and its transpose (Mt) are kept in the A operand's layout.
+__device__ __forceinline__ void strip_transitions(double (&P)[4][1][4], const double *__restrict__ phi, int len) {
+  const int lane = lane_id(), i = lane & 15, q = lane >> 4;
+  double M[4], Mt[4];
+  auto product = [&](const double (&A)[4], const double (&B)[4], double (&R)[4]) {
+    sv4d r = sv4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r = __builtin_amdgcn_mfma_f64_16x16x4f64(A[k], B[k], r, 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) R[k] = r[k];
+  };
+  bool have = false;
+  for (int bits = len, j = 0; bits; bits >>= 1, ++j) {
+    if (!(bits & 1)) continue;
+    const gptr<double> f = (gptr<double>)(phi + (int64_t)j * 256);
+    double F[4], Ft[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      F[k] = f[k * 64 + lane];                                     // F[i][4 k + q]
+      Ft[k] = f[(i >> 2) * 64 + (i & 3) * 16 + 4 * k + q];         // F[4 k + q][i]
+    }
+    if (!have) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        M[k] = F[k];
+        Mt[k] = Ft[k];
+      }
+      have = true;
+    } else {
+      double a[4], b[4];
+      product(Ft, M, a);   // M F
+      product(M, Ft, b);   // its transpose
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        M[k] = a[k];
+        Mt[k] = b[k];
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) P[j][0][k] = M[k];
+    if (j == 3) break;
+    double a[4], b[4];
+    product(Mt, M, a);
+    product(M, Mt, b);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      M[k] = a[k];
+      Mt[k] = b[k];
+    }
+  }
+}
+
 // Start states of 64 strips per wavefront, in 16-strip tiles.  MFMA operands
 // (16x16x4): A lane (i, q) = row i, inner index q; B lane (j, q) = strip j;
 // D register r, lane (j, q) = row 4 r + q.  The inner dimension is time; the
@@ -159,9 +225,14 @@ __device__ __forceinline__ void strip_power(double (&P)[MT][4 * MT], const doubl
 // The matrix cores take 64 cycles per product and SIMD: at 5 tiles and 32
 // samples per step a step lasts 2560 cycles (MT = 1), which is what the next
 // step's loads have to arrive.
-template <typename TI, int MT, bool SCAN>
+//
+// REV: the adjoint's states (kernels_strip_adjoint.hpp), in reversed time.
+// The window is the strip's first samples, the sum up to strip s + 1 the state
+// at the end of strip s; it goes to `rev`, 2K values per strip.
+template <typename TI, int MT, bool SCAN, bool REV = false>
 __device__ __forceinline__ void strip_state(const TI *__restrict__ xs, TI *__restrict__ ys, const StripChan &c,
-                                            int s0, unsigned char *lds) {
+                                            int s0, unsigned char *lds, double *__restrict__ rev = nullptr) {
+  constexpr int T0 = SCAN && !REV ? 1 : 0;   // the first tile of the wavefront's own strips
   typedef StripStage<TI> St;
   typedef typename St::VT VT;
   constexpr int H = SCAN ? 1 : 0, NT = 4 + H, V = St::V, XP = 4 / V;
@@ -177,7 +248,7 @@ __device__ __forceinline__ void strip_state(const TI *__restrict__ xs, TI *__res
 #pragma unroll
   for (int j = 0; j < OPS; ++j) {
     const int row = j * St::ROWS + lane / St::PIECES;
-    at[j] = (uint32_t)((s0 - 16 * H + row) * len - c.lead + (len - c.span)) * (uint32_t)es +
+    at[j] = (uint32_t)((s0 - 16 * T0 + row) * len - c.lead + (REV ? 0 : len - c.span)) * (uint32_t)es +
             16u * (uint32_t)(St::slot(row, lane % St::PIECES) - row * St::PIECES);
   }
   sv4d acc[NT][MT];
@@ -186,7 +257,7 @@ __device__ __forceinline__ void strip_state(const TI *__restrict__ xs, TI *__res
 #pragma unroll
     for (int m = 0; m < MT; ++m) acc[t][m] = sv4d{0.0, 0.0, 0.0, 0.0};
   const int blocks = c.span / kStripBlock;
-  const gptr<vd2> hp = (gptr<vd2>)(c.hop) + (int64_t)(blocks - 1) * (MT * 128) + lane;
+  const gptr<vd2> hp = (gptr<vd2>)(REV ? c.hop_rev : c.hop) + (REV ? 0 : (int64_t)(blocks - 1) * (MT * 128)) + lane;
   struct Step {
     sv4u in[OPS];
     vd2 h[MT][U][2];
@@ -200,11 +271,12 @@ __device__ __forceinline__ void strip_state(const TI *__restrict__ xs, TI *__res
 #pragma unroll
       for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int k = 0; k < 2; ++k) f.h[m][u][k] = hp[(m * 2 + k) * 64 - (int64_t)(U * n + u) * (MT * 128)];
+        for (int k = 0; k < 2; ++k) f.h[m][u][k] = hp[(m * 2 + k) * 64 + (REV ? 1 : -1) * (int64_t)(U * n + u) * (MT * 128)];
   };
   // the step of strip 0 that starts with the channel's start: the samples
   // before it in the same 16 bytes are zeros
-  const int head = s0 == 0 && c.shift > 0 ? (c.lead - (len - c.span)) / (16 * U) : -1;   // uniform
+  // (REV: nothing needs strip 0's sums)
+  const int head = !REV && s0 == 0 && c.shift > 0 ? (c.lead - (len - c.span)) / (16 * U) : -1;   // uniform
   // Through the tile, so that adjacent lanes load adjacent addresses (a load of
   // 16 bytes from each of 64 places takes 64 cycles of the texture unit, which
   // bound this kernel before: 135 us for 64 x 2^20 samples).
@@ -225,7 +297,7 @@ __device__ __forceinline__ void strip_state(const TI *__restrict__ xs, TI *__res
         }
       if (u == 0 && n == head) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) xd[H][k] = lane == 0 && k < c.shift ? 0.0 : xd[H][k];
+        for (int k = 0; k < 3; ++k) xd[T0][k] = lane == 0 && k < c.shift ? 0.0 : xd[T0][k];
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -259,57 +331,79 @@ __device__ __forceinline__ void strip_state(const TI *__restrict__ xs, TI *__res
     // Phi^(len 2^j) for the rounds the run-in needs (past its end, the first
     // one again), all at once where they fit the registers
     constexpr int PN = MT == 1 ? 4 : 1;
+    const double *phi = REV ? c.phi_rev : c.phi;
     double P[PN][MT][4 * MT];
     const int lg = 31 - __builtin_clz((unsigned)len);   // len = 2^lg
+    if (MT == 1 && (len & (len - 1))) {
+      if constexpr (MT == 1) strip_transitions(P, phi, len);
+    } else {
 #pragma unroll
-    for (int j = 0; j < PN; ++j) strip_power<MT>(P[j], c.phi, lg + (c.terms > (1 << j) ? j : 0));
-    // the raw input's history: x[t0-2] and x[t0-1] enter through the first
-    // section's non-recursive stage only (b2, and b1 then b2)
-    const ctab<double> tab = as_ctab(c.tab);
-    const double b1 = tab[OFF_B1], b2 = tab[OFF_B2];
-    double hx[MT];
-#pragma unroll
-    for (int m = 0; m < MT; ++m) {
-      const int k = (16 * m + i) >> 1, d = 1 - (i & 1);
-      const gptr<double> g = (gptr<double>)(c.g + (int64_t)(k < c.K ? k : 0) * c.gstride + len - 1 - d);
-      const double h = q == 2 ? b2 * g[0] : fma_(b1, g[0], b2 * g[-1]);
-      hx[m] = k < c.K && q >= 2 ? h : 0.0;
+      for (int j = 0; j < PN; ++j) strip_power<MT>(P[j], phi, lg + (c.terms > (1 << j) ? j : 0));
     }
+    if constexpr (!REV) {
+      // the raw input's history: x[t0-2] and x[t0-1] enter through the first
+      // section's non-recursive stage only (b2, and b1 then b2)
+      const ctab<double> tab = as_ctab(c.tab);
+      const double b1 = tab[OFF_B1], b2 = tab[OFF_B2];
+      double hx[MT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int s = s0 + 16 * (t - H) + i;
-      double xe = 0.0;
-      if (s > 0 && q >= 2) {
-        const int o4 = s * len - c.lead - 4 + q;
-        const uint32_t o = (uint32_t)o4 * (uint32_t)es;
-        if constexpr (sizeof(TI) == 4) {
-          xe = (double)__uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, o, 0, 0));
-        } else {
-          typedef uint32_t v2u __attribute__((ext_vector_type(2)));
-          xe = __builtin_bit_cast(double, __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(rx, o, 0, 0)));
-        }
-        if (o4 < c.shift) xe = 0.0;
+      for (int m = 0; m < MT; ++m) {
+        const int k = (16 * m + i) >> 1, d = 1 - (i & 1);
+        const gptr<double> g = (gptr<double>)(c.g + (int64_t)(k < c.K ? k : 0) * c.gstride + len - 1 - d);
+        const double h = q == 2 ? b2 * g[0] : fma_(b1, g[0], b2 * g[-1]);
+        hx[m] = k < c.K && q >= 2 ? h : 0.0;
       }
 #pragma unroll
-      for (int m = 0; m < MT; ++m) acc[t][m] = __builtin_amdgcn_mfma_f64_16x16x4f64(hx[m], xe, acc[t][m], 0, 0, 0);
+      for (int t = 0; t < NT; ++t) {
+        const int s = s0 + 16 * (t - T0) + i;
+        double xe = 0.0;
+        if (s > 0 && q >= 2) {
+          const int o4 = s * len - c.lead - 4 + q;
+          const uint32_t o = (uint32_t)o4 * (uint32_t)es;
+          if constexpr (sizeof(TI) == 4) {
+            xe = (double)__uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, o, 0, 0));
+          } else {
+            typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+            xe = __builtin_bit_cast(double, __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(rx, o, 0, 0)));
+          }
+          if (o4 < c.shift) xe = 0.0;
+        }
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[t][m] = __builtin_amdgcn_mfma_f64_16x16x4f64(hx[m], xe, acc[t][m], 0, 0, 0);
+      }
     }
     // sums over 2, 4, 8, 16 strips, as far as the run-in reaches
-    strip_round<1, NT, MT>(acc, P[0], i);
+    strip_round<1, NT, MT, REV>(acc, P[0], i);
     if (c.terms > 2) {
-      if (PN == 1) strip_power<MT>(P[0], c.phi, lg + 1);
-      strip_round<2, NT, MT>(acc, P[1 % PN], i);
+      if (PN == 1) strip_power<MT>(P[0], phi, lg + 1);
+      strip_round<2, NT, MT, REV>(acc, P[1 % PN], i);
     }
     if (c.terms > 4) {
-      if (PN == 1) strip_power<MT>(P[0], c.phi, lg + 2);
-      strip_round<4, NT, MT>(acc, P[2 % PN], i);
+      if (PN == 1) strip_power<MT>(P[0], phi, lg + 2);
+      strip_round<4, NT, MT, REV>(acc, P[2 % PN], i);
     }
     if (c.terms > 8) {
-      if (PN == 1) strip_power<MT>(P[0], c.phi, lg + 3);
-      strip_round<8, NT, MT>(acc, P[3 % PN], i);
+      if (PN == 1) strip_power<MT>(P[0], phi, lg + 3);
+      strip_round<8, NT, MT, REV>(acc, P[3 % PN], i);
     }
   }
   // the sum up to strip s is the state at the start of strip s + 1; sums that
   // need more than 16 strips go next to it, in strip s, for the scan kernel
+  if constexpr (REV) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int s = s0 + 16 * t + i, d = s - 1;
+      // this wavefront's 64 end states (SCAN), or its 64 strips' own sums
+      if (d < 0 || s >= (int)c.strips || (SCAN && (d < s0 || d >= s0 + kStripLanes))) continue;
+      double *o = rev + (int64_t)d * 2 * c.K;
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (16 * m + 4 * r + q < 2 * c.K) o[16 * m + 4 * r + q] = acc[t][m][r];
+    }
+    return;
+  }
   const bool part = SCAN && c.terms > 16;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -439,9 +533,12 @@ __device__ __forceinline__ void strip_section(double (&X)[C], const double (&t)[
 // with the coefficients in scalar registers too; KT = 16 serves any K up to
 // 16 (a branch per section), with each section's coefficients loaded during
 // the one before it.
-template <typename TI, int KT>
+// CKPT: also writes every section's state at the start of every chunk to
+// `ckpt`, a buffer laid out like x (128 bytes per chunk, K <= 8); !STORE: no
+// outputs (ys only holds the start states).
+template <typename TI, int KT, bool CKPT = false, bool STORE = true>
 __device__ __forceinline__ void strip_filter(const TI *__restrict__ xs, TI *__restrict__ ys, const StripChan &c,
-                                             int64_t s0, unsigned char *lds) {
+                                             int64_t s0, unsigned char *lds, TI *__restrict__ ckpt = nullptr) {
   typedef StripStage<TI> St;
   typedef typename St::VT VT;
   constexpr int V = St::V, C = St::C;
@@ -470,6 +567,9 @@ __device__ __forceinline__ void strip_filter(const TI *__restrict__ xs, TI *__re
   // past its end: one code path for every chunk, so that a wait for a chunk's
   // loads counts exactly the accesses issued after them.
   const __amdgpu_buffer_rsrc_t rx = strip_rsrc(xs, c), ry = strip_rsrc(ys, c);
+  // the checkpoints' buffer ends on a whole chunk and starts with the channel
+  const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+      ckpt, 0, (int)(uint32_t)(((c.n + c.shift) * (int64_t)sizeof(TI) + 127) / 128 * 128), 0x00020000);
   uint32_t at[St::OPS];   // byte offset of the lane's piece of op j
 #pragma unroll
   for (int j = 0; j < St::OPS; ++j) {
@@ -525,6 +625,17 @@ __device__ __forceinline__ void strip_filter(const TI *__restrict__ xs, TI *__re
       for (int i = 0; i < V; ++i)
         if (lane == 0 && i < c.shift) X[i] = 0.0;
     }
+    if constexpr (CKPT) {
+      static_assert(!CKPT || KT <= 8, "one line per checkpoint");
+#pragma unroll
+      for (int p = 0; p < KT; ++p) reinterpret_cast<vd2 *>(stage)[St::slot(lane, p)] = ys0[p];
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int j = 0; j < St::OPS; ++j)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(sv4u, stage[j * 64 + lane]), rc,
+                                               at[j] + 128u * (uint32_t)ch, 0, 0);
+      __builtin_amdgcn_wave_barrier();
+    }
     double p2 = xm2, p1 = xm1;
     xm2 = X[C - 2];
     xm1 = X[C - 1];
@@ -549,36 +660,39 @@ __device__ __forceinline__ void strip_filter(const TI *__restrict__ xs, TI *__re
       p2 = y0[0];
       p1 = y0[1];
     }
-    __builtin_amdgcn_wave_barrier();
+    if constexpr (STORE) {
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int p = 0; p < St::PIECES; ++p) {
-      VT v;
+      for (int p = 0; p < St::PIECES; ++p) {
+        VT v;
 #pragma unroll
-      for (int i = 0; i < V; ++i) v[i] = (TI)(X[p * V + i] * c.gain);
-      stage[St::slot(lane, p)] = v;
+        for (int i = 0; i < V; ++i) v[i] = (TI)(X[p * V + i] * c.gain);
+        stage[St::slot(lane, p)] = v;
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (ch == head) {
+        // the first piece also covers samples before the channel's start: its
+        // stores are dropped, and its samples of the channel kept for the end
+        firsts = stage[St::slot(0, 0)];
+      }
+#pragma unroll
+      for (int j = 0; j < St::OPS; ++j)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(sv4u, stage[j * 64 + lane]), ry,
+                                               ch == head && j == 0 && lane == 0 ? 0xffffff00u : at[j] + 128u * (uint32_t)ch,
+                                               0, 0);
+      __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_wave_barrier();
-    if (ch == head) {
-      // the first piece also covers samples before the channel's start: its
-      // stores are dropped, and its samples of the channel kept for the end
-      firsts = stage[St::slot(0, 0)];
-    }
-#pragma unroll
-    for (int j = 0; j < St::OPS; ++j)
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(sv4u, stage[j * 64 + lane]), ry,
-                                             ch == head && j == 0 && lane == 0 ? 0xffffff00u : at[j] + 128u * (uint32_t)ch,
-                                             0, 0);
-    __builtin_amdgcn_wave_barrier();
   };
   // dropped stores, so that the loop is entered with as many accesses behind
   // the loads of chunk 1 as it goes round with, and its waits count the same
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int j = 0; j < St::OPS; ++j) __builtin_amdgcn_raw_buffer_store_b128(sv4u{0, 0, 0, 0}, ry, 0xfffffe00u + 16 * j, 0, 0);
+  for (int j = 0; j < St::OPS * ((CKPT ? 1 : 0) + (STORE ? 1 : 0)); ++j)
+    __builtin_amdgcn_raw_buffer_store_b128(sv4u{0, 0, 0, 0}, ry, 0xfffffc00u + 16 * j, 0, 0);
   __builtin_amdgcn_sched_barrier(0);
   int ch = 0;
   do chunk(ch); while (++ch < chunks);
-  if (head >= 0 && lane < V && lane >= c.shift && lane - c.shift < c.n) {
+  if (STORE && head >= 0 && lane < V && lane >= c.shift && lane - c.shift < c.n) {
     TI v = firsts[0];
 #pragma unroll
     for (int i = 1; i < V; ++i)

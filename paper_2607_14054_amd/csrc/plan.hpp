@@ -85,7 +85,12 @@ struct sos_plan_s {
   std::vector<std::vector<double>> phi_pow;
   double *d_strip = nullptr;
   int strip_span = 0;              // samples the state table covers (a multiple of 16)
+  int strip_rows = 0;              // samples the tables hold: strip_span, or adj_span where that is more
   size_t strip_g = 0, strip_phi = 0;   // doubles from d_strip to the all-pole responses and the powers
+  // the adjoint by strips (sosfilt_strip_adjoint.hip): its tables' samples (0:
+  // the plan keeps the tiles), doubles from d_strip to its state table and powers
+  int adj_span = 0;
+  size_t strip_hop_rev = 0, strip_phi_rev = 0;
 };
 
 namespace sosf {
@@ -129,6 +134,15 @@ sos_status launch_wide(const sos_plan_s &p, const void *x, void *y, int64_t n, v
 bool strip_supported(const sos_plan_s &p);
 sos_status upload_strip(sos_plan_s &p);
 struct StripChan;
+struct AdjStrip;
+// the adjoint by strips (sosfilt_strip_adjoint.hip): whether a plan has its
+// tables, the tables in reversed time, the geometry and launches of a single signal
+bool adj_strip_supported(const sos_plan_s &p);
+void adj_strip_tables(const sos_plan_s &p, double *hop, double *phi);
+bool adj_strip_single(const sos_plan_s &p, int64_t n, size_t room, AdjStrip &d);
+sos_status launch_adj_strip(bool forward, bool adjoint, const sos_plan_s &p, const AdjStrip &d, const void *x, void *y,
+                            const void *gy, void *gx, double *ws, hipStream_t s);
+void strip_cut(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, int span, int64_t terms, StripChan &c);
 bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, StripChan &c);
 bool strip_single(const sos_plan_s &p, int64_t n, int64_t tile, bool scan, StripChan &c);
 sos_status launch_strip(const sos_plan_s &p, const StripChan &c, const void *x, void *y, hipStream_t s);

@@ -333,7 +333,6 @@ sos_status create_plan(const double *sos, int32_t K, const sos_opts *opts, bool 
   }
   if (st == SOS_OK && !(o.flags & SOS_FLAG_HOST_ONLY)) {
     st = upload(*p);
-    if (st == SOS_OK && strip_supported(*p)) st = upload_strip(*p);
     if (st == SOS_OK && carry_supported(*p)) {
       // the transition the exact inter-tile carry raises to the tile length
       const size_t bytes = p->phi.size() * sizeof(double);
@@ -364,6 +363,7 @@ sos_status create_plan(const double *sos, int32_t K, const sos_opts *opts, bool 
     p->simds = r.simds;
     p->waves_per_simd = r.waves_per_simd;
     if (st == SOS_OK && adjoint) st = attach_adjoint(*p, sos);
+    if (st == SOS_OK && strip_supported(*p)) st = upload_strip(*p);   // (the adjoint's run-in sizes the tables)
   }
   if (st != SOS_OK) {
     sos_plan_destroy(p);

@@ -9,6 +9,7 @@
 #include "kernels_backward.hpp"
 #include "plan.hpp"
 #include "batch.hpp"
+#include "strip_types.hpp"
 
 using namespace sosf;
 
@@ -198,7 +199,15 @@ sos_status launch_adjoint(int steps, const sos_plan_s &p, const void *x, void *y
   a.mid_off = l.mid_off;
   const double *tab = static_cast<const double *>(b.d_table);
   const double *rows = static_cast<const double *>(p.d_bwd_rows);
-  if (n > 0) {
+  int64_t sums = n > 0 ? l.ntiles : 0;
+  AdjStrip d;
+  if (adj_strip_single(p, n, l.saved_bytes, d)) {
+    // long signals: one lane per strip of the time axis, in the same workspace
+    const sos_status st = launch_adj_strip(steps & STEP_FORWARD, steps & STEP_ADJOINT, p, d, x, y, gy, gx, saved, s);
+    if (st != SOS_OK) return st;
+    partials = saved + d.part_off;
+    sums = d.waves;
+  } else if (n > 0) {
     // forward-time tiles (saving outputs or checkpoints), then the
     // reversed-time adjoint
     BwdArgs f = a;
@@ -221,7 +230,7 @@ sos_status launch_adjoint(int steps, const sos_plan_s &p, const void *x, void *y
   }
   if (steps & STEP_ADJOINT)
     hipLaunchKernelGGL(sos_adjoint_reduce_kernel, dim3((unsigned)p.K), dim3(kReduceThreads), 0, s, partials,
-                       n > 0 ? l.ntiles : (int64_t)0, (int32_t)p.K, rows, gsos);
+                       sums, (int32_t)p.K, rows, gsos);
   return hipGetLastError() == hipSuccess ? SOS_OK : SOS_E_DEVICE;
 }
 
@@ -269,7 +278,11 @@ template <typename TI>
 sos_status launch_adjoint_batched(int steps, const sos_batch_s &b, const void *x, void *y, const void *gy, void *gx,
                                   double *gsos, void *ws, hipStream_t s) {
   double *w = static_cast<double *>(ws);
-  if (b.adj_items > 0) {
+  if (b.adj_strip_items > 0) {
+    const sos_status st =
+        launch_adj_strip_batched(steps & STEP_FORWARD, steps & STEP_ADJOINT, b, x, y, gy, gx, w, s);
+    if (st != SOS_OK) return st;
+  } else if (b.adj_items > 0) {
     if (b.adj_rc) {
       if (b.adj_b0one)
         launch_batched<TI, true, true>(steps, b, x, y, gy, gx, w, s);
@@ -398,6 +411,7 @@ sos_status schedule_batch_adjoint(sos_batch_s &b, const sos_plan_t *plans, int32
   b.adj_item_chan = std::move(item_chan);
   b.adj_red = std::move(red);
   b.adj = true;
+  if (tile_groups <= 0) adj_strip_schedule(b, plans);
   return SOS_OK;
 }
 

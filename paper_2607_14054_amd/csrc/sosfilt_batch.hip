@@ -256,10 +256,10 @@ sos_status schedule(sos_batch_s &b, const sos_plan_t *plans, int32_t C, const in
 
 // The device descriptors of a schedule, packed into one blob: the header
 // (live item count, generation), forward channels, forward items, adjoint
-// channels, adjoint items, gsos rows.  The regions are sized by the batch's
+// channels, adjoint items, gsos rows, adjoint strips.  The regions are sized by the batch's
 // room, fixed at creation.
 struct BlobLayout {
-  size_t hdr, chans, items, strips, strip_items, adj, adj_items, red, bytes;
+  size_t hdr, chans, items, strips, strip_items, adj, adj_items, red, adj_strips, bytes;
 };
 
 size_t up16(size_t v) { return (v + 15) & ~(size_t)15; }
@@ -274,7 +274,8 @@ BlobLayout blob_layout(size_t C, size_t items, size_t strip_items, size_t adj_it
   l.adj = up16(l.strip_items + strip_items * sizeof(int32_t));
   l.adj_items = up16(l.adj + C * sizeof(AdjChan));
   l.red = up16(l.adj_items + adj_items * sizeof(int32_t));
-  l.bytes = up16(l.red + rows * sizeof(int32_t));
+  l.adj_strips = up16(l.red + rows * sizeof(int32_t));
+  l.bytes = up16(l.adj_strips + (rows ? C : 0) * sizeof(AdjStrip));
   return l;
 }
 
@@ -297,6 +298,8 @@ void pack(const sos_batch_s &b, const BlobLayout &l, unsigned char *dst) {
     std::memcpy(dst + l.adj, b.adj_chans.data(), b.adj_chans.size() * sizeof(AdjChan));
     std::memcpy(dst + l.adj_items, b.adj_item_chan.data(), b.adj_item_chan.size() * sizeof(int32_t));
     std::memcpy(dst + l.red, b.adj_red.data(), b.adj_red.size() * sizeof(int32_t));
+    if (b.adj_strip_items > 0)
+      std::memcpy(dst + l.adj_strips, b.adj_strips.data(), b.adj_strips.size() * sizeof(AdjStrip));
   }
 }
 
@@ -310,6 +313,7 @@ void point(sos_batch_s &b, const BlobLayout &l) {
     b.d_adj = nullptr;
     b.d_adj_item = nullptr;
     b.d_adj_red = nullptr;
+    b.d_adj_strips = nullptr;
     return;
   }
   b.d_hdr = reinterpret_cast<const int64_t *>(b.d_blob + l.hdr);
@@ -320,7 +324,12 @@ void point(sos_batch_s &b, const BlobLayout &l) {
   b.d_adj = reinterpret_cast<AdjChan *>(b.d_blob + l.adj);
   b.d_adj_item = reinterpret_cast<int32_t *>(b.d_blob + l.adj_items);
   b.d_adj_red = reinterpret_cast<int32_t *>(b.d_blob + l.red);
+  b.d_adj_strips = reinterpret_cast<AdjStrip *>(b.d_blob + l.adj_strips);
 }
+
+// The adjoint's items, by tiles or (where it takes them) by strips: the room
+// covers both, as a replan's channels may go either way.
+int64_t adj_items_of(const sos_batch_s &b) { return b.adj ? std::max(b.adj_items, b.adj_strip_items) : 0; }
 
 // Room for channel sets of up to C channels and `samples` samples in all:
 // tiles of at least one group give at most samples / (4 G) + 2 C work items
@@ -332,7 +341,7 @@ void reserve_room(sos_batch_s &b, int64_t C, int64_t samples, int kmax) {
   const int64_t Gb = (int64_t)kBwdN * kL;
   b.C_cap = (int32_t)std::max<int64_t>(C, b.C);
   b.items_cap = std::max<int64_t>(samples / (R * G) + 2 * C + 1, b.items);
-  b.adj_items_cap = std::max<int64_t>((samples + 3 * C) / (4 * Gb) + 2 * C + 1, b.adj ? (int64_t)b.adj_item_chan.size() : 0);
+  b.adj_items_cap = std::max<int64_t>((samples + 3 * C) / (4 * Gb) + 2 * C + 1, adj_items_of(b));
   b.kmax_cap = std::max(kmax, b.kmax);
   b.rows_cap = std::max<int64_t>(C * (int64_t)b.kmax_cap, b.adj ? (int64_t)b.adj_red.size() : 0);
 }
@@ -347,7 +356,7 @@ sos_status fits(const sos_batch_s &b, const sos_batch_s &t) {
   if (t.C > b.C_cap || t.items > b.items_cap || t.kmax > b.kmax_cap) return SOS_E_NOMEM;
   if (t.strip_items > b.strip_cap || (t.strip_scan && !b.strip_scan_cap)) return SOS_E_NOMEM;
   if (t.adj != b.adj) return SOS_E_UNSUPPORTED;
-  if (t.adj && ((int64_t)t.adj_item_chan.size() > b.adj_items_cap || (int64_t)t.adj_red.size() > b.rows_cap))
+  if (t.adj && (adj_items_of(t) > b.adj_items_cap || (int64_t)t.adj_red.size() > b.rows_cap))
     return SOS_E_NOMEM;
   return SOS_OK;
 }
@@ -364,7 +373,7 @@ bool batch_descriptors_valid(const sos_batch_s &b) {
   };
   return inside(b.d_hdr) && inside(b.d_chans) && inside(b.d_item_chan) && inside(b.d_strips) &&
          (b.strip_cap == 0 || inside(b.d_strip_item)) && inside(b.d_adj) && inside(b.d_adj_item) &&
-         inside(b.d_adj_red);
+         inside(b.d_adj_red) && (b.adj_strip_items == 0 || inside(b.d_adj_strips));
 }
 
 extern "C" {
@@ -402,7 +411,7 @@ sos_status sos_batch_plan(const sos_plan_t *plans, int32_t C, const int64_t *n,
   } else {
     b->C_cap = C;
     b->items_cap = b->items;
-    b->adj_items_cap = b->adj ? (int64_t)b->adj_item_chan.size() : 0;
+    b->adj_items_cap = adj_items_of(*b);
     b->kmax_cap = b->kmax;
     b->rows_cap = b->adj ? (int64_t)b->adj_red.size() : 0;
     b->inst_b0one = b->b0one;
@@ -463,6 +472,7 @@ sos_status sos_batch_replan(sos_batch_t b, const sos_plan_t *plans, int32_t C, c
   sos_batch_s t;
   t.host_only = b->host_only;
   t.tile_groups = b->tile_groups;
+  if (!b->host_only) t.adj_strip_room = b->adj_items_cap;
   st = schedule(t, plans, C, n, offsets, b->tile_groups);
   if (st != SOS_OK) return st;
   // a device batch keeps its room and its launch; a host-only batch is only

@@ -69,10 +69,12 @@ void square_powers(sos_plan_s &p) {
 //     section's recursive part (h_k = g_k + b1 g_k[. - 1] + b2 g_k[. - 2]).
 sos_status upload_strip(sos_plan_s &p) {
   const int K = p.K, D = 2 * K, mt = (D + 15) / 16, R = 16 * mt;
-  const int span = (int)std::min<int64_t>((p.runin + 31) / 32 * 32, kStripMaxSpan);
-  const int gs = span + 16;
+  auto covering = [](int64_t runin) { return (int)std::min<int64_t>((runin + 31) / 32 * 32, kStripMaxSpan); };
+  p.strip_span = covering(p.runin);
+  p.adj_span = adj_strip_supported(p) ? covering(std::max(p.runin, p.bwd->runin)) : 0;
+  const int span = p.strip_rows = std::max(p.strip_span, p.adj_span), gs = span + 16;
   const size_t hop = (size_t)span * R, gsz = (size_t)K * gs, psz = p.phi_pow.size() * (size_t)R * R;
-  std::vector<double> t(hop + gsz + psz, 0.0);
+  std::vector<double> t((hop + psz) * (p.adj_span ? 2 : 1) + gsz, 0.0);
   double *g = t.data() + hop, *ph = g + gsz;
   // every section per sample, so that the sections' recurrences overlap
   std::vector<double> state(4 * (size_t)K, 0.0);   // per section: input x1, x2, output y1, y2
@@ -120,16 +122,48 @@ sos_status upload_strip(sos_plan_s &p) {
     for (int i = 0; i < D; ++i)
       for (int j = 0; j < D; ++j)   // the A operand's order: [row tile][step][lane]
         ph[q * R * R + (size_t)(i / 16 * 4 * mt + j / 4) * 64 + j % 4 * 16 + i % 16] = p.phi_pow[q][(size_t)i * D + j];
+  if (p.adj_span) adj_strip_tables(p, ph + psz, ph + psz + hop);
   if (hipMalloc(&p.d_strip, t.size() * sizeof(double)) != hipSuccess) {
     p.d_strip = nullptr;
     return SOS_E_NOMEM;
   }
   if (hipMemcpy(p.d_strip, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
     return SOS_E_DEVICE;
-  p.strip_span = span;
   p.strip_g = hop;
   p.strip_phi = hop + gsz;
+  p.strip_hop_rev = p.strip_phi + psz;
+  p.strip_phi_rev = p.strip_hop_rev + hop;
   return SOS_OK;
+}
+
+// Strips of len samples over [-shift, n), their start states summed over
+// `terms` strips of `span` samples.
+void strip_cut(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, int span, int64_t terms, StripChan &c) {
+  const int64_t es = p.io_dtype == SOS_F64 ? 8 : 4;
+  const int mt = (2 * p.K + 15) / 16;
+  const int64_t area = (16 * mt * 8 + 16) / es;   // samples of one state area with its alignment
+  const int64_t rem = (n + shift) % len;
+  const int64_t lead = rem > 0 && rem < area ? (area - rem + 31) / 32 * 32 : 0;
+  c.tab = static_cast<const double *>(p.d_table);
+  c.hop = p.d_strip;
+  c.g = p.d_strip + p.strip_g;
+  c.phi = p.d_strip + p.strip_phi;
+  c.hop_rev = p.d_strip + p.strip_hop_rev;
+  c.phi_rev = p.d_strip + p.strip_phi_rev;
+  c.off = 0;
+  c.n = n;
+  c.len = len;
+  c.strips = (n + shift + lead + len - 1) / len;
+  c.first_item = 0;
+  c.K = p.K;
+  c.stride = p.stride;
+  c.shift = shift;
+  c.span = span;
+  c.terms = (int32_t)terms;
+  c.mt = mt;
+  c.gstride = p.strip_rows + 16;
+  c.lead = (int32_t)lead;
+  c.gain = p.gain;
 }
 
 // Strips of about `len` samples over [-shift, n).
@@ -137,8 +171,8 @@ bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, 
   if (!p.d_strip) return false;
   const int64_t es = p.io_dtype == SOS_F64 ? 8 : 4;
   const int mt = (2 * p.K + 15) / 16;
-  // samples of one state area with its alignment; a strip holds two, and the lead
-  const int64_t area = (16 * mt * 8 + 16) / es, least = 3 * area + 32;
+  // a strip holds two state areas with their alignment, and the lead
+  const int64_t least = 3 * ((16 * mt * 8 + 16) / es) + 32;
   // The state table covers the run-in, so a strip that long needs one term;
   // shorter strips are powers of two (their transition is a table entry), at
   // most 2 KB, so that a long signal has two wavefronts per SIMD.
@@ -155,26 +189,7 @@ bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, 
     len = std::min(l, most);
     if (len > p.strip_span || len < least || (p.runin + len - 1) / len > kStripMaxTerms) return false;
   }
-  const int64_t rem = (n + shift) % len;
-  const int64_t lead = rem > 0 && rem < area ? (area - rem + 31) / 32 * 32 : 0;
-  c.tab = static_cast<const double *>(p.d_table);
-  c.hop = p.d_strip;
-  c.g = p.d_strip + p.strip_g;
-  c.phi = p.d_strip + p.strip_phi;
-  c.off = 0;
-  c.n = n;
-  c.len = len;
-  c.strips = (n + shift + lead + len - 1) / len;
-  c.first_item = 0;
-  c.K = p.K;
-  c.stride = p.stride;
-  c.shift = shift;
-  c.span = (int32_t)(covers ? p.strip_span : len);
-  c.terms = covers ? 1 : (int32_t)((p.runin + len - 1) / len);
-  c.mt = mt;
-  c.gstride = p.strip_span + 16;
-  c.lead = (int32_t)lead;
-  c.gain = p.gain;
+  strip_cut(p, n, shift, len, (int)(covers ? p.strip_span : len), covers ? 1 : (p.runin + len - 1) / len, c);
   // 32-bit byte offsets, with the strips past the end
   return (n + 96 * len) * es < ((int64_t)1 << 32);
 }

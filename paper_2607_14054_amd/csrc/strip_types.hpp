@@ -23,6 +23,8 @@ struct StripChan {
   const double *hop;       // state table, in the order the products read it (upload_strip)
   const double *g;         // all-pole responses, [K][gstride]
   const double *phi;       // padded powers Phi^(2^j) in the A operand's order
+  const double *hop_rev;   // the adjoint's state table and powers, in reversed time
+  const double *phi_rev;
   int64_t off, n;          // first sample in x / y, length
   int64_t len, strips;     // samples per strip (a multiple of 32; a power of two where terms > 1), strips
   int64_t first_item;      // first work item (64 strips) of the channel
@@ -38,5 +40,18 @@ struct StripChan {
 };
 
 static_assert(sizeof(StripChan) % 8 == 0, "copied by 64-bit words");
+
+// The adjoint of a channel by strips: the forward's strips, and its regions
+// of the workspace (in doubles).
+constexpr int kAdjStripK = 8;
+struct AdjStrip {
+  StripChan c;
+  const double *bwd;       // adjoint rows (BW_*)
+  int64_t ck_off;          // checkpoints: 128 bytes per 128 bytes of signal
+  int64_t rev_off;         // states at the strips' ends, 2K per strip
+  int64_t part_off;        // coefficient sums, [K][waves][5]
+  int64_t waves;           // wavefronts of 64 strips
+};
+static_assert(sizeof(AdjStrip) % 8 == 0, "copied by 64-bit words");
 
 }  // namespace sosf

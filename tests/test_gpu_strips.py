@@ -191,3 +191,70 @@ def test_strips_batch_graph_and_replans():
                 launch()
             stream.synchronize()
             _check_batch(y.cpu().numpy(), xb, sos, lengths, offsets, "f32")
+
+
+def row_err(g, ref):
+    scale = np.maximum(np.max(np.abs(ref), axis=1, keepdims=True), 1e-300)
+    return float(np.max(np.abs(g - ref) / scale))
+
+
+def check_adjoint(sos, x, g, gx, gs):
+    # the bars of the FP32 adjoint paths: dL/dx 1e-6, dL/dsos 1e-9 of its row
+    lx, ls = oracle.sosfilt_backward_ld(x, sos, g)
+    assert not np.isnan(gx).any()
+    ex, es = oracle.rel_rms(gx, lx), row_err(gs, ls)
+    assert ex < 1e-6, ex
+    assert es < 1e-9, es
+
+
+# strips of 96 samples, one sample more, a last strip just below and at the
+# length that holds its start state, longer ones (96, 160), the length that 16 strips of a long run-in need (r = 0.99, 0.998), and a run-in
+# inside one strip (6.6e7 samples: 1024 a strip)
+@pytest.mark.parametrize("n,r_hi", [(21846 * 96, 0.9), (21846 * 96 + 1, 0.95), (21846 * 96 + 35, 0.9),
+                                    (21846 * 96 + 36, 0.9), (6000001, 0.95), (10000003, 0.9), (2100007, 0.99),
+                                    (2100007, 0.998), (66000001, 0.9)])
+def test_adjoint_strips(n, r_hi):
+    sos = W.make_sos(8, 0.5, r_hi, 960)
+    x, g = W.make_signal(n, 961, np.float32), W.grad_seed_signal(n, 961, np.float32)
+    p = S.Plan(sos, io_dtype="f32")
+    xt, gt = torch.from_numpy(x).to(DEV), torch.from_numpy(g).to(DEV)
+    gx, gs = S.filt_backward(p, xt, gt, gx=torch.full_like(xt, float("nan")))
+    y, ws = S.filt_for_backward(p, xt)
+    gx2, gs2 = S.filt_backward_stored(p, xt, gt, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(gx, gx2) and torch.equal(gs, gs2)
+    check_adjoint(sos, x, g, gx.cpu().numpy(), gs.cpu().numpy())
+    assert oracle.rel_rms(y.cpu().numpy(), oracle.sosfilt(x, sos)) < 1e-6
+
+
+def test_adjoint_strips_batched():
+    """Ragged channels at every offset mod 4 with gaps between them, long and
+    short run-ins in one batch, and a replan to other lengths."""
+    ns, his = [400001, 70000, 64, 262144, 300003, 150002, 4099, 500000], [0.9, 0.95, 0.9, 0.99, 0.95, 0.9, 0.98, 0.9]
+    soss = [W.make_sos(8, 0.5, hi, 970 + i) for i, hi in enumerate(his)]
+    plans = [S.Plan(s, io_dtype="f32") for s in soss]
+    off, at = [], 0
+    for i, n in enumerate(ns):
+        off.append(at)
+        at += n + (1, 2, 3, 5, 0, 7, 4, 6)[i]
+    b = S.Batch(plans, ns, offsets=off)
+    for lens in (ns, [n - 37 if n > 100 else n for n in ns]):
+        if lens is not ns:
+            b.replan(plans, lens, offsets=off)
+        x, g = W.make_signal(b.total, 971, np.float32), W.grad_seed_signal(b.total, 971, np.float32)
+        xt, gt = torch.from_numpy(x).to(DEV), torch.from_numpy(g).to(DEV)
+        y, ws = S.filt_batched_for_backward(b, xt)
+        gx = torch.full_like(xt, 7.0)
+        out = S.filt_backward_batched_stored(b, xt, gt, ws, gx=gx)
+        one = S.filt_backward_batched(b, xt, gt, gx=torch.full_like(xt, 7.0))
+        torch.cuda.synchronize()
+        gs = out[1]
+        assert torch.equal(out[0], one[0])
+        gx = gx.cpu().numpy()
+        covered = np.zeros(b.total, bool)
+        for i, (o, n) in enumerate(zip(off, lens)):
+            covered[o:o + n] = True
+            gi = gs[8 * i:8 * i + 8]
+            check_adjoint(soss[i], x[o:o + n], g[o:o + n], gx[o:o + n], gi.cpu().numpy())
+            assert oracle.rel_rms(y[o:o + n].cpu().numpy(), oracle.sosfilt(x[o:o + n], soss[i])) < 1e-6
+        assert (gx[~covered] == 7.0).all()   # the gaps are left alone
