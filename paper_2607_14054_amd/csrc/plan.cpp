@@ -212,21 +212,22 @@ sos_status build_plan_tables(sos_plan_s &p, const double *sos) {
   const int64_t NL = (int64_t)N * p.L;
   p.warm = ((W + NL - 1) / NL) * NL;
   // the norm over the rounded length, for reporting
+  const size_t powers = pw.size();
   {
     std::vector<double> r;
     int64_t rem = p.warm;
-    std::vector<double> base = p.phi;
     bool have = false;
     for (int j = 0; rem && j < 62; ++j) {
       if (rem & 1) {
-        r = have ? matmul(r, base, D) : base;
+        r = have ? matmul(r, pw[j], D) : pw[j];
         have = true;
       }
       rem >>= 1;
-      if (rem) base = matmul(base, base, D);
+      if (rem && j + 1 == (int)pw.size()) pw.push_back(matmul(pw[j], pw[j], D));
     }
     p.warm_norm = have ? inf_norm(r, D) : 1.0;
   }
+  pw.resize(powers);
   if (strip_supported(p)) p.phi_pow = std::move(pw);
   return SOS_OK;
 }

@@ -22,27 +22,29 @@ namespace {
 
 bool pow2_in(int v, int lo, int hi) { return v >= lo && v <= hi && (v & (v - 1)) == 0; }
 
+// The section tables, the solvers and (where the exact inter-tile carry raises
+// it to the tile length) the one-step transition, in one allocation and one
+// copy: each of those takes the driver some 10 us.
 sos_status upload(sos_plan_s &p) {
   if (hipGetDevice(&p.device) != hipSuccess) return SOS_E_DEVICE;
   const size_t count = (size_t)p.K * p.stride;
   const size_t esz = p.compute_dtype == SOS_F64 ? 8 : 4;
-  if (hipMalloc(&p.d_table, count * esz) != hipSuccess) { p.d_table = nullptr; return SOS_E_NOMEM; }
-  if (hipMalloc(&p.d_solver, (size_t)p.K * sizeof(int32_t)) != hipSuccess) {
-    hipFree(p.d_table);
-    p.d_table = nullptr;
-    p.d_solver = nullptr;
-    return SOS_E_NOMEM;
-  }
-  hipError_t e1, e2;
+  const size_t phi = carry_supported(p) ? p.phi.size() * sizeof(double) : 0;
+  const size_t solver_at = (count * esz + 255) / 256 * 256;
+  const size_t phi_at = (solver_at + (size_t)p.K * sizeof(int32_t) + 255) / 256 * 256;
+  std::vector<unsigned char> host(phi_at + phi);
   if (esz == 8) {
-    e1 = hipMemcpy(p.d_table, p.table.data(), count * 8, hipMemcpyHostToDevice);
+    std::memcpy(host.data(), p.table.data(), count * 8);
   } else {
-    std::vector<float> f(count);
+    float *f = reinterpret_cast<float *>(host.data());
     for (size_t i = 0; i < count; ++i) f[i] = (float)p.table[i];
-    e1 = hipMemcpy(p.d_table, f.data(), count * 4, hipMemcpyHostToDevice);
   }
-  e2 = hipMemcpy(p.d_solver, p.solver.data(), (size_t)p.K * sizeof(int32_t), hipMemcpyHostToDevice);
-  if (e1 != hipSuccess || e2 != hipSuccess) return SOS_E_DEVICE;
+  std::memcpy(host.data() + solver_at, p.solver.data(), (size_t)p.K * sizeof(int32_t));
+  if (phi) std::memcpy(host.data() + phi_at, p.phi.data(), phi);
+  if (hipMalloc(&p.d_table, host.size()) != hipSuccess) { p.d_table = nullptr; return SOS_E_NOMEM; }
+  p.d_solver = static_cast<unsigned char *>(p.d_table) + solver_at;
+  if (phi) p.d_phi = static_cast<unsigned char *>(p.d_table) + phi_at;
+  if (hipMemcpy(p.d_table, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess) return SOS_E_DEVICE;
   if (p.solver_opt == SOS_PH_DEFERRED) {
     const size_t nt = p.theta_mfma.size(), nc = p.coupling.size() ? p.coupling.size() : 1;
     if (hipMalloc(&p.d_theta, nt * 8) != hipSuccess) { p.d_theta = nullptr; return SOS_E_NOMEM; }
@@ -333,16 +335,6 @@ sos_status create_plan(const double *sos, int32_t K, const sos_opts *opts, bool 
   }
   if (st == SOS_OK && !(o.flags & SOS_FLAG_HOST_ONLY)) {
     st = upload(*p);
-    if (st == SOS_OK && carry_supported(*p)) {
-      // the transition the exact inter-tile carry raises to the tile length
-      const size_t bytes = p->phi.size() * sizeof(double);
-      if (hipMalloc(&p->d_phi, bytes) != hipSuccess) {
-        p->d_phi = nullptr;
-        st = SOS_E_NOMEM;
-      } else if (hipMemcpy(p->d_phi, p->phi.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
-        st = SOS_E_DEVICE;
-      }
-    }
     Residency r;
     if (st == SOS_OK && p->solver_opt == SOS_PH_DEFERRED && !wide_plan(*p))
       r = p->io_dtype == SOS_F32 ? deferred_residency<float>(p->N, p->K, p->b0_factored)
@@ -377,18 +369,16 @@ extern "C" {
 
 sos_status sos_plan_destroy(sos_plan_t p) {
   if (!p) return SOS_OK;
-  if (p->d_table || p->d_solver) {
+  if (p->d_table) {
     int cur = -1;
     hipGetDevice(&cur);
     if (p->device >= 0 && cur != p->device) hipSetDevice(p->device);
-    if (p->d_table) hipFree(p->d_table);
-    if (p->d_solver) hipFree(p->d_solver);
+    hipFree(p->d_table);   // with the solvers and the transition
     if (p->d_theta) hipFree(p->d_theta);
     if (p->d_coupling) hipFree(p->d_coupling);
     if (p->d_bwd_rows) hipFree(p->d_bwd_rows);
     if (p->d_block) hipFree(p->d_block);
     if (p->d_aop) hipFree(p->d_aop);
-    if (p->d_phi) hipFree(p->d_phi);
     if (p->d_strip) hipFree(p->d_strip);
     if (p->device >= 0 && cur >= 0 && cur != p->device) hipSetDevice(cur);
   }

@@ -44,11 +44,11 @@ void square_powers(sos_plan_s &p) {
     }
   }
   for (size_t q = 1; q < p.phi_pow.size(); ++q) {
-    std::fill(b.begin(), b.end(), 0.0L);
     for (int i = 0; i < D; ++i)
-      for (int k = 0; k < (i | 1) + 1; ++k) {
-        const long double v = a[(size_t)i * D + k];
-        for (int j = 0; j < (k | 1) + 1; ++j) b[(size_t)i * D + j] += v * a[(size_t)k * D + j];
+      for (int j = 0; j < (i | 1) + 1; ++j) {
+        long double sum = 0.0L;
+        for (int k = j & ~1; k < (i | 1) + 1; ++k) sum += a[(size_t)i * D + k] * a[(size_t)k * D + j];
+        b[(size_t)i * D + j] = sum;
       }
     a.swap(b);
     for (int i = 0; i < D * D; ++i) p.phi_pow[q][i] = (double)a[i];
