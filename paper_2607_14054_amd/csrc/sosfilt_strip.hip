@@ -141,7 +141,7 @@ sos_status upload_strip(sos_plan_s &p) {
 void strip_cut(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, int span, int64_t terms, StripChan &c) {
   const int64_t es = p.io_dtype == SOS_F64 ? 8 : 4;
   const int mt = (2 * p.K + 15) / 16;
-  const int64_t area = (16 * mt * 8 + 16) / es;   // samples of one state area with its alignment
+  const int64_t area = 16 * mt * 8 / es;   // samples of one state area
   const int64_t rem = (n + shift) % len;
   const int64_t lead = rem > 0 && rem < area ? (area - rem + 31) / 32 * 32 : 0;
   c.tab = static_cast<const double *>(p.d_table);
@@ -171,11 +171,16 @@ bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, 
   if (!p.d_strip) return false;
   const int64_t es = p.io_dtype == SOS_F64 ? 8 : 4;
   const int mt = (2 * p.K + 15) / 16;
-  // a strip holds two state areas with their alignment, and the lead
-  const int64_t least = 3 * ((16 * mt * 8 + 16) / es) + 32;
-  // The state table covers the run-in, so a strip that long needs one term;
-  // shorter strips are powers of two (their transition is a table entry), at
-  // most 2 KB, so that a long signal has two wavefronts per SIMD.
+  // a strip holds two state areas and, strip 0, the lead and the 16 bytes
+  // before its first whole ones
+  const int64_t areas = 2 * (16 * mt * 8 / es) + 16 / es, least = areas + 32;
+  // The state table covers the run-in, so a strip that long needs one term.
+  // Shorter ones, at most 2 KB so that a long signal has two wavefronts per
+  // SIMD: any multiple of 32 where the kernel makes their transition (FP32 I/O,
+  // K <= 8, up to 16 strips' sums), so that every lane has one strip; otherwise
+  // powers of two, whose transition is a table entry, down to 7/8 of that
+  // rather than twice as many (9e6 FP32 samples, K = 8, r <= 0.9: 128 a strip
+  // 52 us, 160: 39).
   const bool covers = p.runin <= p.strip_span && len >= p.strip_span;
   if (covers) {
     // (off the multiples of 2 KB: strips a power of two apart meet in few HBM
@@ -184,9 +189,17 @@ bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, 
     if (len * es % 2048 == 0) len += 32;
   } else {
     const int64_t most = 2048 / es;
-    int64_t l = 32;
-    while (2 * l <= len || l < least) l *= 2;
-    len = std::min(l, most);
+    const int64_t any = (std::max({len, least, (p.runin + 15) / 16}) + 31) / 32 * 32;
+    if (p.io_dtype == SOS_F32 && mt == 1 && any <= len + 31 && any < most && any <= p.strip_span &&
+        any >> p.phi_pow.size() == 0) {
+      len = any;
+    } else {
+      int64_t l = 32;
+      while (2 * l <= len * 8 / 7 || l < least) l *= 2;
+      strip_cut(p, n, shift, l, (int)l, 1, c);
+      if (l - c.lead < areas) l *= 2;
+      len = std::min(l, most);
+    }
     if (len > p.strip_span || len < least || (p.runin + len - 1) / len > kStripMaxTerms) return false;
   }
   strip_cut(p, n, shift, len, (int)(covers ? p.strip_span : len), covers ? 1 : (p.runin + len - 1) / len, c);
@@ -196,31 +209,32 @@ bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, 
 
 // Strips for a single signal of n samples, where they beat the tile kernels.
 // Measured against PH at N = 64 (MI355X, us, tiles / strips):
-//   FP32 I/O, K = 8 (r <= 0.98): 7e6 samples 43 / 53, 1.2e7 66 / 53, 3.3e7
-//     121 / 90, 1e8 325 / 245; K = 3: 1.2e7 45 / 43, 3.3e7 97 / 71; K = 12:
-//     2e7 124 / 147, 3.3e7 152 / 125, 1e8 408 / 288;
-//   FP64 I/O, K = 8: 3e6 53 / 40, 2^24 + 5 148 / 88, 5e7 300 / 279; K = 3:
-//     1.2e7 64 / 72, 2.5e7 122 / 145; K = 12: 2.5e7 182 / 191, 5e7 340 / 279;
+//   FP32 I/O, r <= 0.98: K = 5, 1.05e6 samples 25 / 25, 1.5e6 30 / 26, 5e6 39 /
+//     28, 2e7 86 / 57; K = 8, 1.5e6 50 / 30, 9e6 87 / 39, 3e7 130 / 83; K = 4,
+//     1.05e6 24 / 25, 1.5e6 28 / 26; K = 2, 7e6 24 / 26, 9e6 49 / 33; K = 12,
+//     2e7 124 / 147, 3.3e7 152 / 125;
+//   FP64 I/O: K = 8, 1.5e6 39 / 32, 2^24 + 5 148 / 88; K = 5, 1.05e6 28 / 29,
+//     1.5e6 33 / 30; K = 3, 1.2e7 64 / 72; K = 12, 2.5e7 182 / 191, 5e7 340 /
+//     279;
 //   poles up to r = 0.999, where the tiles carry by the scan or run in over
-//     more than a tile (K = 8): FP32 3e6 59 / 56, 1.2e7 114 / 64, FP64 3e6
-//     62 / 48, 2^24 + 5 204 / 101.
+//     more than a tile: K = 8, FP32 2^18 53 / 34, 2^20 52 / 35, FP64 2^20 54 /
+//     39; K = 4, FP32 2^18 31 / 30; K = 2, FP32 2^20 28 / 29, 3e6 41 / 32; K =
+//     12, FP32 4.2e6 66 / 76, 9e6 149 / 94, FP64 2^20 79 / 67; K = 16, FP32 3e6
+//     95 / 84.
 // With FP32 I/O the tiles keep signals that they share out evenly in powers of
-// two, where they are at their best (2^26: 175 us against 236; 2^28, launch
-// after launch: 611 against 618).
+// two, where they are at their best (K = 5, 2^22: 22 us against 28; 2^26: 175
+// against 236; 2^28, launch after launch: 611 against 618).
 bool strip_single(const sos_plan_s &p, int64_t n, int64_t tile, bool scan, StripChan &c) {
   if (!p.d_strip) return false;
   const bool f64 = p.io_dtype == SOS_F64, slow = scan || p.warm > tile;
-  const int64_t least = slow ? 3000000
-                             : (f64 ? (p.K <= 4 ? INT64_MAX : (p.K <= 8 ? 1 << 21 : 40000000))
-                                    : (p.K <= 8 ? 10000000 : 30000000));
+  const int64_t least = slow ? (f64 || p.K <= 8 ? (p.K <= 3 ? 3000000 : 1 << 18) : (p.K <= 14 ? 7000000 : 3000000))
+                             : (f64 ? (p.K <= 4 ? INT64_MAX : (p.K <= 8 ? 1400000 : 40000000))
+                                    : (p.K <= 3 ? 8000000 : (p.K <= 4 ? 1400000 : (p.K <= 8 ? 1000000 : 30000000))));
   if (n < least) return false;
   const int64_t lanes = (int64_t)p.simds * 64, len = (n + lanes - 1) / lanes;
-  const bool covers = p.runin <= p.strip_span && len >= p.strip_span;
   const int64_t groups = tile / ((int64_t)p.N * p.L);
   if (!f64 && !slow && (groups & (groups - 1)) == 0 && n % (tile * 4 * p.simds) == 0) return false;
-  // shorter strips than the run-in are powers of two: down to 7/8 of a
-  // wavefront per SIMD rather than twice as many
-  return strip_geometry(p, n, 0, covers ? len : len * 8 / 7, c);
+  return strip_geometry(p, n, 0, len, c);
 }
 
 namespace {

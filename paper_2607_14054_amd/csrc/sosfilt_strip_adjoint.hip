@@ -75,10 +75,9 @@ void adj_strip_tables(const sos_plan_s &p, double *hop, double *phi) {
 
 namespace {
 
-// A state area is 36 samples (2K doubles, 16-byte alignment) and the lead that
-// makes room for one in the last strip a multiple of 32, at most 64: below 96 a
-// strip could hold less than the lead and the area's rest.
-constexpr int64_t kLeastLen = 96;
+// A state area is 32 samples, and the lead that makes room for one in the last
+// strip as many: shorter strips have no room for both.
+constexpr int64_t kLeastLen = 64;
 
 // Strips of about `len` samples and their regions from `base` on, in doubles;
 // false where the run-in needs more than 16 strips or the regions `room`.

@@ -26,7 +26,7 @@ struct StripChan {
   const double *hop_rev;   // the adjoint's state table and powers, in reversed time
   const double *phi_rev;
   int64_t off, n;          // first sample in x / y, length
-  int64_t len, strips;     // samples per strip (a multiple of 32; a power of two where terms > 1), strips
+  int64_t len, strips;     // strip length (a multiple of 32; a power of two where terms > 16, or > 1 and mt = 2), strips
   int64_t first_item;      // first work item (64 strips) of the channel
   int32_t K, stride;
   int32_t shift;           // off mod the samples per 16 bytes

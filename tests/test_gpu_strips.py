@@ -58,7 +58,19 @@ def test_strips_slow_poles(io, K):
     check(run(sos, x, io), x, sos, io)
 
 
-@pytest.mark.parametrize("K,r_hi,n", [(1, 0.9, 10000003), (8, 0.95, 16777216 + 36), (3, 0.98, 33000001),
+@pytest.mark.parametrize("io", ["f64", "f32"])
+@pytest.mark.parametrize("n", [1 << 18, (1 << 18) + 1, (1 << 18) + 3, (1 << 18) + 31, (1 << 18) + 32, 300001])
+@pytest.mark.parametrize("K", [4, 8, 12])
+def test_strips_slow_poles_short(io, n, K):
+    """From 2^18 samples in strips of 128 (K <= 8): a last strip of one sample,
+    and just below and at a state's room (32 samples, FP64 16)."""
+    sos = W.make_sos(K, 0.9, 0.999, 915 + K)
+    x = W.make_signal(n, 916, np.float64 if io == "f64" else np.float32)
+    check(run(sos, x, io), x, sos, io)
+
+
+@pytest.mark.parametrize("K,r_hi,n", [(1, 0.9, 10000003), (5, 0.95, 1500001), (8, 0.98, 5000003),
+                                      (6, 0.95, 9000002), (2, 0.98, 20000031), (8, 0.95, 16777216 + 36), (3, 0.98, 33000001),
                                       (12, 0.95, 30000005), (16, 0.9, 67108864 + 61)])
 def test_strips_f32(K, r_hi, n):
     """FP32 from 1e7 samples (3e7 for K > 8): run-ins over several strips and
@@ -207,11 +219,12 @@ def check_adjoint(sos, x, g, gx, gs):
     assert es < 1e-9, es
 
 
-# strips of 96 samples, one sample more, a last strip just below and at the
+# strips of 64 samples, one sample more, a last strip just below and at the
 # length that holds its start state, longer ones (96, 160), the length that 16 strips of a long run-in need (r = 0.99, 0.998), and a run-in
 # inside one strip (6.6e7 samples: 1024 a strip)
 @pytest.mark.parametrize("n,r_hi", [(21846 * 96, 0.9), (21846 * 96 + 1, 0.95), (21846 * 96 + 35, 0.9),
-                                    (21846 * 96 + 36, 0.9), (6000001, 0.95), (10000003, 0.9), (2100007, 0.99),
+                                    (21846 * 96 + 36, 0.9), (21846 * 96 + 31, 0.9),
+                                    (21846 * 96 + 32, 0.9), (6000001, 0.95), (10000003, 0.9), (2100007, 0.99),
                                     (2100007, 0.998), (66000001, 0.9)])
 def test_adjoint_strips(n, r_hi):
     sos = W.make_sos(8, 0.5, r_hi, 960)
