@@ -14,7 +14,7 @@
 //     eight over a line's first half, for its second half's states);
 //   * per section mu (two FMA), the five sums of the coefficient gradients
 //     (five) and lambda (two), the sums kept per lane over the whole strip.
-// That is 134 FP64 instructions per sample and no scan over lanes; the tiles'
+// That is 133 FP64 instructions per sample and no scan over lanes; the tiles'
 // adjoint issues 259 per sample, and a run-in per tile.  One wavefront per
 // SIMD: 512 registers hold the four sections' signals (160), lambda (32), 40
 // sums (80), 16 states (32) and three lines in flight (96).  Bound by FP64

@@ -179,8 +179,9 @@ bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, 
   // SIMD: any multiple of 32 where the kernel makes their transition (FP32 I/O,
   // K <= 8, up to 16 strips' sums), so that every lane has one strip; otherwise
   // powers of two, whose transition is a table entry, down to 7/8 of that
-  // rather than twice as many (9e6 FP32 samples, K = 8, r <= 0.9: 128 a strip
-  // 52 us, 160: 39).
+  // rather than twice as many, but not 128 for more than a wavefront per SIMD
+  // (1.2e7 FP32 samples, K = 5, r <= 0.999: 128 a strip 68 us, 2e7 in 256: 58;
+  // 9e6, K = 8, r <= 0.9: 128 a strip 52, 160: 39).
   const bool covers = p.runin <= p.strip_span && len >= p.strip_span;
   if (covers) {
     // (off the multiples of 2 KB: strips a power of two apart meet in few HBM
@@ -195,7 +196,7 @@ bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, 
       len = any;
     } else {
       int64_t l = 32;
-      while (2 * l <= len * 8 / 7 || l < least) l *= 2;
+      while (2 * l <= len * 8 / 7 || l < least || (l == 128 && len > 128)) l *= 2;
       strip_cut(p, n, shift, l, (int)l, 1, c);
       if (l - c.lead < areas) l *= 2;
       len = std::min(l, most);
@@ -207,34 +208,49 @@ bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, 
   return (n + 96 * len) * es < ((int64_t)1 << 32);
 }
 
-// Strips for a single signal of n samples, where they beat the tile kernels.
-// Measured against PH at N = 64 (MI355X, us, tiles / strips):
-//   FP32 I/O, r <= 0.98: K = 5, 1.05e6 samples 25 / 25, 1.5e6 30 / 26, 5e6 39 /
-//     28, 2e7 86 / 57; K = 8, 1.5e6 50 / 30, 9e6 87 / 39, 3e7 130 / 83; K = 4,
-//     1.05e6 24 / 25, 1.5e6 28 / 26; K = 2, 7e6 24 / 26, 9e6 49 / 33; K = 12,
-//     2e7 124 / 147, 3.3e7 152 / 125;
-//   FP64 I/O: K = 8, 1.5e6 39 / 32, 2^24 + 5 148 / 88; K = 5, 1.05e6 28 / 29,
-//     1.5e6 33 / 30; K = 3, 1.2e7 64 / 72; K = 12, 2.5e7 182 / 191, 5e7 340 /
-//     279;
-//   poles up to r = 0.999, where the tiles carry by the scan or run in over
-//     more than a tile: K = 8, FP32 2^18 53 / 34, 2^20 52 / 35, FP64 2^20 54 /
-//     39; K = 4, FP32 2^18 31 / 30; K = 2, FP32 2^20 28 / 29, 3e6 41 / 32; K =
-//     12, FP32 4.2e6 66 / 76, 9e6 149 / 94, FP64 2^20 79 / 67; K = 16, FP32 3e6
-//     95 / 84.
+// Strips for a single signal of n samples, where they beat the tile kernels
+// (which N = 16 and 32 shorten, so that odd sizes share out better).  Measured
+// against PH (MI355X, us, tiles / strips):
+//   poles up to r = 0.999, where the tiles carry by the scan: FP32, K = 8, 2^18
+//     41 .. 55 (N = 16 .. 64) / 33, 2^20 43 .. 52 / 35, 9e6 86 .. 107 / 43; K =
+//     4, 2^18 29 .. 35 / 29; K = 2, 3e6 28 / 31 (N = 64: 41 / 32), 5e6 34 / 34;
+//     K = 12, 4e6 66 / 76 (N = 64), 9e6 126 / 81; K = 16, 3e6 95 / 84; FP64, K =
+//     8, 2^18 40 .. 55 / 36; K = 5, r = 0.98, 1.5e6 29 / 31, 2.1e6 38 / 32; K =
+//     12, 2^18 58 (N = 16) .. 94 (N = 64) / 62, 2^20 66 / 65;
+//   run-ins, FP32, N = 64: K = 5, 1.05e6 25 / 25, 5e6 39 / 28, 2e7 86 / 57; K =
+//     4, 1.05e6 24 / 25, 1.5e6 28 / 26; K = 2, 7e6 24 / 26, 9e6 49 / 33; K = 12,
+//     2e7 124 / 147, 3.3e7 152 / 125; N = 32: K = 4, 5e6 24 / 26, 9e6 40 / 34;
+//     K = 3, 1.6e7 44 / 47, 2e7 59 / 46; N = 16: K = 4, 1.2e7 33 / 40, 1.6e7 48
+//     / 47; K = 8, 9e6 41 / 39, 1.2e7 50 / 46; N <= 32, K = 2: 5e7 92 / 101;
+//   run-ins, FP64, N = 64: K = 8, 1.5e6 39 / 32, 2^24 + 5 148 / 88; K = 5, 1.05e6
+//     28 / 29, 1.5e6 33 / 30, 4e7 204 / 230; K = 3, 1.2e7 64 / 72; K = 12, 2.5e7 182 / 191, 5e7
+//     340 / 279; N = 32: K = 8, 9e6 52 / 56, 1.2e7 62 / 58, 4e7 206 / 232; K = 5,
+//     1.2e7 53 / 58, 2^24 + 5 91 / 78; N = 16: K = 5, 2^24 + 5 73 / 78.
 // With FP32 I/O the tiles keep signals that they share out evenly in powers of
-// two, where they are at their best (K = 5, 2^22: 22 us against 28; 2^26: 175
-// against 236; 2^28, launch after launch: 611 against 618).
+// two, where they are at their best (N = 64, K = 5, 2^22: 22 us against 28; 2^26:
+// 175 against 236; 2^28, launch after launch: 611 against 618).
 bool strip_single(const sos_plan_s &p, int64_t n, int64_t tile, bool scan, StripChan &c) {
   if (!p.d_strip) return false;
-  const bool f64 = p.io_dtype == SOS_F64, slow = scan || p.warm > tile;
-  const int64_t least = slow ? (f64 || p.K <= 8 ? (p.K <= 3 ? 3000000 : 1 << 18) : (p.K <= 14 ? 7000000 : 3000000))
-                             : (f64 ? (p.K <= 4 ? INT64_MAX : (p.K <= 8 ? 1400000 : 40000000))
-                                    : (p.K <= 3 ? 8000000 : (p.K <= 4 ? 1400000 : (p.K <= 8 ? 1000000 : 30000000))));
-  if (n < least) return false;
-  const int64_t lanes = (int64_t)p.simds * 64, len = (n + lanes - 1) / lanes;
-  const int64_t groups = tile / ((int64_t)p.N * p.L);
-  if (!f64 && !slow && (groups & (groups - 1)) == 0 && n % (tile * 4 * p.simds) == 0) return false;
-  return strip_geometry(p, n, 0, len, c);
+  constexpr int64_t kNever = INT64_MAX;
+  const bool f64 = p.io_dtype == SOS_F64, wide = p.N == 64;
+  const int K = p.K;
+  int64_t least, most = kNever;
+  if (scan) {
+    if (f64) least = K <= 3 ? (wide ? 3000000 : 5000000) : K <= 6 ? (wide ? 300000 : 2000000) : K <= 8 || wide ? 1 << 18 : 1000000;
+    else least = K <= 3 ? (wide ? 3000000 : 5000000) : K <= 8 ? 1 << 18 : K <= 14 ? 7000000 : 3000000;
+  } else if (f64) {
+    if (wide) least = K <= 4 ? kNever : K <= 8 ? 1400000 : 40000000;
+    else least = K <= 4 || K > 8 ? kNever : K > 6 ? 11000000 : p.N == 32 ? 14000000 : kNever;
+  } else {
+    if (wide) least = K <= 3 ? 8000000 : K <= 4 ? 1400000 : K <= 8 ? 1000000 : 30000000;
+    else least = K <= 3 ? 18000000 : K > 8 ? 30000000 : p.N == 32 ? 8000000 : K <= 6 ? 16000000 : 10000000;
+  }
+  if (f64 && (!wide || K <= 6)) most = 30000000;
+  if (!f64 && !wide && K <= 6) most = 40000000;
+  if (n < least || n > most) return false;
+  const int64_t lanes = (int64_t)p.simds * 64, groups = tile / ((int64_t)p.N * p.L);
+  if (!f64 && !scan && (groups & (groups - 1)) == 0 && n % (tile * 4 * p.simds) == 0) return false;
+  return strip_geometry(p, n, 0, (n + lanes - 1) / lanes, c);
 }
 
 namespace {
