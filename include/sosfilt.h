@@ -187,7 +187,9 @@ sos_status sos_plan_query(sos_plan_t plan, sos_plan_info *info, int32_t *solver)
  * plan's tile_groups, or the launch-shape model: the shortest tile that
  * gives every SIMD at most m wavefronts (four tiles each), m the largest
  * power of two of resident wavefronts per SIMD for the plan's kernel.  The
- * exact carry (see sos_workspace_size) uses the same model with no run-in. */
+ * exact carry (see sos_workspace_size) uses the same model with no run-in.
+ * (Where sos_filt cuts a SOS_AUTO plan's signal into strips, one per lane,
+ * this is the tile it would use otherwise.) */
 int64_t sos_plan_tile(sos_plan_t plan, int64_t n);
 
 /* Host FP64 tables, for inspection and tests.  Copies min(count, size) values
@@ -231,7 +233,11 @@ sos_status sos_plan_table(sos_plan_t plan, int32_t table, int32_t section,
  * tiles (a signal short against its run-in, poles near the unit circle) and
  * the run-in it saves, K (W - tile) section-samples, is at least 8192 (below
  * that the scan's extra launches cost more), or always with
- * SOS_FLAG_CARRY_SCAN; never with SOS_FLAG_CARRY_RUNIN.
+ * SOS_FLAG_CARRY_SCAN; never with SOS_FLAG_CARRY_RUNIN.  Long signals of
+ * SOS_AUTO plans without those flags (FP64 arithmetic, K <= 16, L = 16, N = 8 ..
+ * 64, no tile_groups) are cut into strips instead, one per lane, with exact
+ * start states to the run-in's bound, where that is faster; strips need no
+ * workspace, and the size stays the same.
  */
 size_t sos_workspace_size(sos_plan_t plan, int64_t n);
 
@@ -282,7 +288,8 @@ sos_status sos_filt_static(sos_plan_t plan, const void *x, void *y, int64_t n, s
  * same tile kernels (Sections V to VII) run on every channel, and only the
  * scheduling is shared: each channel is cut into tiles, four tiles form one
  * wavefront's work item, and the items of all channels are launched
- * together, costliest first.
+ * together, costliest first.  (SOS_AUTO plans with long run-ins go by strips,
+ * as in sos_filt, 64 strips to a work item.)
  *
  * sos_batch_plan -- fix the channel set and lengths once (allocates).
  *
@@ -443,7 +450,9 @@ size_t sos_backward_workspace_size(sos_plan_t plan, int64_t n);
  * workspace  device, sos_backward_workspace_size(plan, n) bytes, 16-byte
  *            aligned; its contents on entry do not matter.
  * The adjoint always runs PH with FP64 arithmetic at N = 16, whatever the
- * plan's solver, N and compute dtype (the same cascade, exact to rounding).
+ * plan's solver, N and compute dtype (the same cascade, exact to rounding), or
+ * (long signals of SOS_AUTO plans with FP32 I/O and K = 8, no adjoint flag) the
+ * plain recurrences with one strip of the signal per lane.
  * It first re-runs the forward pass (saving section outputs or group
  * states, as above), so the caller's forward result is not needed.  Sums
  * over the signal are formed per tile and added in a fixed order: results
