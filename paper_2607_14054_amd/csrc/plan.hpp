@@ -129,7 +129,7 @@ int64_t wide_tile(const sos_plan_s &p, int64_t n);
 size_t wide_workspace(const sos_plan_s &p, int64_t n);
 sos_status launch_wide(const sos_plan_s &p, const void *x, void *y, int64_t n, void *ws, hipStream_t s);
 // strips (sosfilt_strip.hip): whether a plan has the tables, the geometry of
-// n samples in strips of about len, whether a single signal takes them (tile,
+// n samples in strips of about len (sound: what the kernels assume), whether a single signal takes them (tile,
 // scan: what the tile kernels would run), the launches
 bool strip_supported(const sos_plan_s &p);
 sos_status upload_strip(sos_plan_s &p);
@@ -143,6 +143,7 @@ bool adj_strip_single(const sos_plan_s &p, int64_t n, size_t room, AdjStrip &d);
 sos_status launch_adj_strip(bool forward, bool adjoint, const sos_plan_s &p, const AdjStrip &d, const void *x, void *y,
                             const void *gy, void *gx, double *ws, hipStream_t s);
 void strip_cut(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, int span, int64_t terms, StripChan &c);
+bool strip_sound(const sos_plan_s &p, const StripChan &c);
 bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, StripChan &c);
 bool strip_single(const sos_plan_s &p, int64_t n, int64_t tile, bool scan, StripChan &c);
 sos_status launch_strip(const sos_plan_s &p, const StripChan &c, const void *x, void *y, hipStream_t s);

@@ -166,6 +166,18 @@ void strip_cut(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, int s
   c.gain = p.gain;
 }
 
+// Whether a cut keeps what the kernels assume, whatever branch chose its length:
+// the lead leaves strip 0 a whole state area (with that, strip 1 starts in the
+// channel and the channel's first chunk is strip 0's), the last strip holds its
+// start state, and where more than 16 strips are summed, every strip a second area.
+bool strip_sound(const sos_plan_s &p, const StripChan &c) {
+  const int64_t es = p.io_dtype == SOS_F64 ? 8 : 4, V = 16 / es, area = 16 * c.mt * 8 / es;
+  const int64_t last = c.n + c.shift + c.lead - (c.strips - 1) * c.len;
+  if (c.strips < 1 || last < 1 || last > c.len) return false;
+  if (c.strips == 1) return c.lead < c.len;
+  return last >= area && c.len - c.lead >= (c.terms > 16 ? V + 2 * area : 32) && c.len >= (c.terms > 16 ? 2 : 1) * area;
+}
+
 // Strips of about `len` samples over [-shift, n).
 bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, StripChan &c) {
   if (!p.d_strip) return false;
@@ -173,7 +185,7 @@ bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, 
   const int mt = (2 * p.K + 15) / 16;
   // a strip holds two state areas and, strip 0, the lead and the 16 bytes
   // before its first whole ones
-  const int64_t areas = 2 * (16 * mt * 8 / es) + 16 / es, least = areas + 32;
+  const int64_t area = 16 * mt * 8 / es, areas = 2 * area + 16 / es, least = areas + 32;
   // The state table covers the run-in, so a strip that long needs one term.
   // Shorter ones, at most 2 KB so that a long signal has two wavefronts per
   // SIMD: any multiple of 32 where the kernel makes their transition (FP32 I/O,
@@ -185,8 +197,11 @@ bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, 
   const bool covers = p.runin <= p.strip_span && len >= p.strip_span;
   if (covers) {
     // (off the multiples of 2 KB: strips a power of two apart meet in few HBM
-    // channels; K = 3 on 2^26 FP32 samples, 1024 a strip: 167 us, 1184: 132)
-    len = (len + 31) / 32 * 32;
+    // channels; K = 3 on 2^26 FP32 samples, 1024 a strip: 167 us, 1184: 132).
+    // Sections without poles, or with poles near 0, have run-ins shorter than a
+    // state area: the lead of up to `area` samples, rounded up to 32, then still
+    // has to leave the last strip an area.
+    len = (std::max(len, area + 32) + 31) / 32 * 32;
     if (len * es % 2048 == 0) len += 32;
   } else {
     const int64_t most = 2048 / es;
@@ -205,7 +220,7 @@ bool strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t len, 
   }
   strip_cut(p, n, shift, len, (int)(covers ? p.strip_span : len), covers ? 1 : (p.runin + len - 1) / len, c);
   // 32-bit byte offsets, with the strips past the end
-  return (n + 96 * len) * es < ((int64_t)1 << 32);
+  return strip_sound(p, c) && (n + 96 * len) * es < ((int64_t)1 << 32);
 }
 
 // Strips for a single signal of n samples, where they beat the tile kernels

@@ -100,7 +100,8 @@ bool adj_strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t l
   d.ck_off = base;
   d.rev_off = base + (n + shift + 31) / 32 * (2 * kAdjStripK);
   d.part_off = d.rev_off + d.c.strips * 2 * kAdjStripK;
-  return d.part_off + 5 * kAdjStripK * d.waves <= base + room && (n + 96 * len) * 4 < ((int64_t)1 << 32);
+  return strip_sound(p, d.c) && d.part_off + 5 * kAdjStripK * d.waves <= base + room &&
+         (n + 96 * len) * 4 < ((int64_t)1 << 32);
 }
 
 // Whether `waves` wavefronts of strips of up to `len` samples beat the tiles

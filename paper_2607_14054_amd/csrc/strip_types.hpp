@@ -16,8 +16,9 @@ constexpr int kStripLanes = 64;          // strips per wavefront of the filter k
 
 // A channel (or a single signal) cut into strips of `len` samples over
 // [-shift - lead, n); strip s starts at s * len - lead - shift.  The samples
-// before 0 are zeros; the lead, a multiple of 32 below len, keeps the last
-// strip long enough for its start state.
+// before 0 are zeros; the lead, a multiple of 32 that leaves at least 32 samples
+// of strip 0, keeps the last strip long enough for its start state
+// (strip_sound).
 struct StripChan {
   const double *tab;       // the plan's section rows
   const double *hop;       // state table, in the order the products read it (upload_strip)

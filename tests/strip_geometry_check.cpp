@@ -1,0 +1,102 @@
+// Host sweep of the strip geometry (csrc/sosfilt_strip.hip): every cut that the
+// library would launch keeps what the strip kernels assume.  No GPU: plans are
+// host-only, with a placeholder for the device tables.  Prints each violation
+// and the number of cuts looked at; exits 1 if there was one.
+#include <algorithm>
+#include <cmath>
+#include <cstdio>
+#include <vector>
+
+#include "../paper_2607_14054_amd/csrc/plan.hpp"
+#include "../paper_2607_14054_amd/csrc/strip_types.hpp"
+
+using namespace sosf;
+
+namespace {
+
+int64_t looked = 0, bad = 0, shortest = INT64_MAX;
+
+// r = 0: sections without poles
+sos_plan_t make(int K, double r, int io, int N) {
+  std::vector<double> s;
+  for (int k = 0; k < K; ++k) {
+    const double th = 0.3 + 2.5 * k / K, ph = 2.9 - 2.3 * k / K;
+    const double row[6] = {1.0, -2.0 * std::cos(ph), 1.0, 1.0, -2.0 * r * std::cos(th), r * r};
+    s.insert(s.end(), row, row + 6);
+  }
+  sos_opts o{io, SOS_F64, SOS_AUTO, N, 16, 0, SOS_FLAG_HOST_ONLY};
+  sos_plan_t p = nullptr;
+  if (create_plan(s.data(), K, &o, false, &p, 0.0) != SOS_OK) std::abort();
+  static double placeholder[2];
+  p->d_strip = placeholder;
+  p->strip_span = p->strip_rows = (int)std::min<int64_t>((p->runin + 31) / 32 * 32, kStripMaxSpan);
+  return p;
+}
+
+void fail(const char *what, const sos_plan_s &p, const StripChan &c) {
+  if (++bad <= 20)
+    std::printf("%s: io %d K %d runin %lld n %lld shift %d: len %lld lead %d strips %lld span %d terms %d\n", what,
+                p.io_dtype, p.K, (long long)p.runin, (long long)c.n, c.shift, (long long)c.len, c.lead,
+                (long long)c.strips, c.span, c.terms);
+}
+
+void check(const sos_plan_s &p, const StripChan &c, int64_t runin) {
+  ++looked;
+  const int64_t es = p.io_dtype == SOS_F64 ? 8 : 4, V = 16 / es, area = 16 * c.mt * 8 / es;
+  const int64_t end = c.n + c.shift + c.lead, last = end - (c.strips - 1) * c.len;
+  shortest = std::min(shortest, c.len);
+  if (c.len % 32 || c.lead % 32 || c.span % 32 || c.span > c.len) fail("granularity", p, c);
+  if (c.lead < 0 || c.lead >= c.len) fail("the lead fills strip 0", p, c);
+  if (last <= 0 || last > c.len) fail("strip count", p, c);
+  if (c.strips > 1 && last < area) fail("no room for the last strip's start state", p, c);
+  if (c.strips > 1 && c.len - c.lead - c.shift < 0) fail("strip 1 starts before the signal", p, c);
+  if (c.len < (c.terms > 16 ? 2 : 1) * area) fail("no room for a strip's states", p, c);
+  if (c.terms > 16 && V + 2 * area > c.len - c.lead) fail("no room for strip 0's sums", p, c);
+  if ((c.terms == 1 ? (int64_t)c.span : c.terms * c.len) < runin) fail("run-in not covered", p, c);
+  if (c.terms > 1 && c.span != c.len) fail("sums over parts of strips", p, c);
+  if ((c.terms > 16 || (c.terms > 1 && (c.mt == 2 || es == 8))) && (c.len & (c.len - 1))) fail("power of two", p, c);
+  if ((c.strips + 80) * c.len * es >= (int64_t)1 << 32) fail("32-bit offsets", p, c);
+}
+
+}  // namespace
+
+int main() {
+  const double radii[] = {0.0, 0.02, 0.2, 0.3, 0.5, 0.9, 0.98, 0.999};
+  for (int io : {SOS_F32, SOS_F64})
+    for (int K : {1, 4, 5, 8, 9, 12, 16})
+      for (double r : radii) {
+        sos_plan_t p = make(K, r, io, 64);
+        StripChan c;
+        // channels of a batch: any length, any offset, any length of strip
+        for (int64_t want : {1, 17, 32, 33, 48, 64, 65, 96, 100, 128, 160, 255, 256, 300, 512, 700, 1024, 1100, 2048})
+          for (int64_t base : {(int64_t)16384, (int64_t)40000, (int64_t)1 << 20})
+            for (int64_t rem = 0; rem < 2 * std::min<int64_t>(want, 160) + 130; ++rem)
+              for (int shift = 0; shift < (io == SOS_F64 ? 2 : 4); ++shift)
+                if (strip_geometry(*p, base + rem, shift, want, c)) check(*p, c, p->runin);
+        // single signals by the rule, at every remainder around whole strips per lane
+        for (int N : {16, 32, 64}) {
+          p->N = N;
+          const int64_t lanes = (int64_t)p->simds * 64;
+          for (int64_t per : {4, 16, 22, 31, 32, 33, 46, 64, 65, 128, 200, 400, 600, 1100})
+            for (int64_t d = -130; d <= 130; ++d)
+              for (bool scan : {false, true}) {
+                const int64_t n = per * lanes + d;
+                if (strip_single(*p, n, (int64_t)N * 16 * 3, scan, c)) check(*p, c, p->runin);
+              }
+        }
+        // the adjoint of single signals (FP32, K = 8)
+        if (io == SOS_F32 && K == kAdjStripK) {
+          p->N = 64;
+          p->bwd = make(K, r, io, 16);
+          for (double eps = 0x1p-40; eps > 0x1p-50; eps /= 2) p->bwd->runin += p->bwd->runin / 40;
+          p->adj_span = (int)std::min<int64_t>((p->bwd->runin + 31) / 32 * 32, kStripMaxSpan);
+          p->strip_rows = std::max(p->strip_span, p->adj_span);
+          AdjStrip d;
+          for (int64_t per : {22, 23, 32, 33, 64, 65, 96, 128, 200, 400, 600, 1100})
+            for (int64_t off = -70; off <= 70; ++off)
+              if (adj_strip_single(*p, per * p->simds * 64 + off, (size_t)1 << 40, d)) check(*p, d.c, p->bwd->runin);
+        }
+      }
+  std::printf("%lld cuts, shortest strip %lld, %lld bad\n", (long long)looked, (long long)shortest, (long long)bad);
+  return bad != 0 || looked < 100000;
+}
