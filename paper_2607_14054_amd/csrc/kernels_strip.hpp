@@ -713,20 +713,22 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_filter_kernel(co
   strip_filter<TI, KT>(xs, ys, c, (item - c.first_item) * kStripLanes, smem + (size_t)w * StripStage<TI>::BYTES);
 }
 
-// Batches: the workgroups before `rows_blocks` filter the channels that stay
-// with the tiles (their serial chains start first and finish beside the
-// strips), the others 64 strips per wavefront.  Where the batch's present
-// channels have no strips (a replan), every workgroup takes tiles.
+// Batches: the last workgroups, as many as the live strips need, take 64 strips
+// per wavefront; all before them filter the channels that stay with the tiles
+// (their serial chains start first and finish beside the strips), in turn where
+// there are more tile items than wavefronts.  The split follows the present
+// channels, as a replan moves them between the two; the launch holds a
+// workgroup more than its strips can take (launch_batched).
 template <int N, typename TI>
 __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_batched_kernel(
     const TI *__restrict__ xs, TI *__restrict__ ys, const BatchChan *__restrict__ chans,
-    const int32_t *__restrict__ item_chan, const int64_t *__restrict__ hdr, int32_t kmax, int32_t rows_blocks,
-    StripArgs a) {
+    const int32_t *__restrict__ item_chan, const int64_t *__restrict__ hdr, int32_t kmax, StripArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const bool strips = as_ctab(a.items_live)[0] > 0;
-  if (!strips || (int)blockIdx.x < rows_blocks) {
-    const int64_t step = (int64_t)(strips ? rows_blocks : (int)gridDim.x) * kWavesPerBlock;
+  const int rows_blocks =
+      (int)gridDim.x - (int)((as_ctab(a.items_live)[0] + kWavesPerBlock - 1) / kWavesPerBlock);
+  if ((int)blockIdx.x < rows_blocks) {
+    const int64_t step = (int64_t)rows_blocks * kWavesPerBlock;
     for (int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + w; item < hdr[0]; item += step)
       batched_rows<N, TI, double, true, SOS_PH, kL>(xs, ys, chans, item_chan, item, kmax, smem);
     return;

@@ -410,7 +410,9 @@ sos_status launch_batched(const sos_batch_s &b, const void *x, void *y, hipStrea
   a.item_chan = b.d_strip_item;
   a.items_live = b.d_hdr + 2;
   const unsigned blocks = (unsigned)((b.strip_cap + kWavesPerBlock - 1) / kWavesPerBlock);
-  const unsigned rows = (unsigned)((b.strip_rows_cap + kWavesPerBlock - 1) / kWavesPerBlock);
+  // (a batch whose channels all took strips may be replanned to some by tiles)
+  const unsigned rows =
+      (unsigned)std::max<int64_t>((b.strip_rows_cap + kWavesPerBlock - 1) / kWavesPerBlock, 1);
   hipLaunchKernelGGL((strip_state_batched_kernel<TI>), dim3(blocks), dim3(256), 0, s, xi, yi, a);
   if (b.strip_scan_cap) {
     hipLaunchKernelGGL((strip_scan_kernel<TI, 1>), dim3((unsigned)b.strip_cap), dim3(256), 0, s, yi, a);
@@ -418,7 +420,7 @@ sos_status launch_batched(const sos_batch_s &b, const void *x, void *y, hipStrea
   }
   const size_t lds = std::max(strip_lds_bytes<TI>(), (size_t)lds_bytes<N, TI, double, kL>(b.kmax_cap));
   hipLaunchKernelGGL((strip_batched_kernel<N, TI>), dim3(rows + blocks), dim3(256), lds, s, xi, yi, b.d_chans,
-                     b.d_item_chan, b.d_hdr, (int32_t)b.kmax_cap, (int32_t)rows, a);
+                     b.d_item_chan, b.d_hdr, (int32_t)b.kmax_cap, a);
   return hipGetLastError() == hipSuccess ? SOS_OK : SOS_E_DEVICE;
 }
 
