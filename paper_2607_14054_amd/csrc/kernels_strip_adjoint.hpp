@@ -233,12 +233,14 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 1) void strip_adjoint_kernel(c
     const double h2 = (double)hist[0], h1 = (double)hist[1];
     __builtin_amdgcn_wave_barrier();
     if (ch == head && lane == 0) {
-      // the samples before the channel's start are zeros
-      VT v = tx[St::slot(0, 0)];
+      // the samples before the channel's start are zeros, and so is dL/dy
+      // there: the sums multiply mu by them, and a neighbour's NaN by 0 is NaN
+      VT v = tx[St::slot(0, 0)], g = tg[St::slot(0, 0)];
 #pragma unroll
       for (int i = 0; i < V; ++i)
-        if (i < c.shift) v[i] = TI(0);
+        if (i < c.shift) v[i] = g[i] = TI(0);
       tx[St::slot(0, 0)] = v;
+      tg[St::slot(0, 0)] = g;
     }
     __builtin_amdgcn_wave_barrier();
     fetch(ch > 0 ? ch - 1 : 0);
