@@ -136,9 +136,11 @@ sos_status upload_strip(sos_plan_s &p);
 struct StripChan;
 struct AdjStrip;
 // the adjoint by strips (sosfilt_strip_adjoint.hip): whether a plan has its
-// tables, the tables in reversed time, the geometry and launches of a single signal
+// tables, the tables in reversed time, a batch's strip length, the geometry and
+// launches of a single signal
 bool adj_strip_supported(const sos_plan_s &p);
 void adj_strip_tables(const sos_plan_s &p, double *hop, double *phi);
+int64_t adj_strip_len(const int64_t *n, int C, int64_t total, int64_t longest, int64_t simds);
 bool adj_strip_single(const sos_plan_s &p, int64_t n, size_t room, AdjStrip &d);
 sos_status launch_adj_strip(bool forward, bool adjoint, const sos_plan_s &p, const AdjStrip &d, const void *x, void *y,
                             const void *gy, void *gx, double *ws, hipStream_t s);

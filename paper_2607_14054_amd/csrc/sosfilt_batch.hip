@@ -285,7 +285,9 @@ BlobLayout blob_layout(const sos_batch_s &b) {
                      (size_t)b.rows_cap);
 }
 
-void pack(const sos_batch_s &b, const BlobLayout &l, unsigned char *dst) {
+// Packs a schedule; returns the bytes to copy (the adjoint's strips, last in the
+// blob, only where there are any).
+size_t pack(const sos_batch_s &b, const BlobLayout &l, unsigned char *dst) {
   const int64_t hdr[4] = {b.rows_items, b.gen, b.strip_items, 0};
   std::memcpy(dst + l.hdr, hdr, sizeof(hdr));
   std::memcpy(dst + l.chans, b.chans.data(), b.chans.size() * sizeof(BatchChan));
@@ -301,6 +303,7 @@ void pack(const sos_batch_s &b, const BlobLayout &l, unsigned char *dst) {
     if (b.adj_strip_items > 0)
       std::memcpy(dst + l.adj_strips, b.adj_strips.data(), b.adj_strips.size() * sizeof(AdjStrip));
   }
+  return b.adj_strip_items > 0 ? l.bytes : l.adj_strips;
 }
 
 void point(sos_batch_s &b, const BlobLayout &l) {
@@ -447,8 +450,8 @@ sos_status sos_batch_plan(const sos_plan_t *plans, int32_t C, const int64_t *n,
       delete b;
       return SOS_E_DEVICE;
     }
-    pack(*b, l, b->h_blob);
-    if (hipMemcpy(b->d_blob, b->h_blob, l.bytes, hipMemcpyHostToDevice) != hipSuccess) {
+    const size_t used = pack(*b, l, b->h_blob);
+    if (hipMemcpy(b->d_blob, b->h_blob, used, hipMemcpyHostToDevice) != hipSuccess) {
       free_device(b);
       delete b;
       return SOS_E_DEVICE;
@@ -521,9 +524,9 @@ sos_status sos_batch_replan(sos_batch_t b, const sos_plan_t *plans, int32_t C, c
     if (l.bytes > b->blob_cap) return SOS_E_NOMEM;
     // the staging copy is free once the previous upload has been read
     if (hipEventSynchronize(b->copied) != hipSuccess) return SOS_E_DEVICE;
-    pack(t, l, b->h_blob);
+    const size_t used = pack(t, l, b->h_blob);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (hipMemcpyAsync(b->d_blob, b->h_blob, l.bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
+    if (hipMemcpyAsync(b->d_blob, b->h_blob, used, hipMemcpyHostToDevice, s) != hipSuccess ||
         hipEventRecord(b->copied, s) != hipSuccess)
       return SOS_E_DEVICE;
     point(t, l);

@@ -78,6 +78,7 @@ namespace {
 // A state area is 32 samples, and the lead that makes room for one in the last
 // strip as many: shorter strips have no room for both.
 constexpr int64_t kLeastLen = 64;
+constexpr int64_t kAdjLeastTotal = 1500000;   // samples (adj_strip_pays)
 
 // Strips of about `len` samples and their regions from `base` on, in doubles;
 // false where the run-in needs more than 16 strips or the regions `room`.
@@ -115,9 +116,8 @@ bool adj_strip_geometry(const sos_plan_s &p, int64_t n, int32_t shift, int64_t l
 // / 220 (idle lanes: the ratio of the rounds' samples to the signals' is 4);
 // 64 x 2^18 356 / 245.
 bool adj_strip_pays(const sos_plan_s &p, int64_t runin, int64_t total, int64_t waves, int64_t len) {
-  constexpr int64_t kLeastTotal = 1500000;
   const int64_t rounds = (waves + p.simds - 1) / p.simds;
-  return total >= kLeastTotal && (double)(rounds * p.simds * kStripLanes * len) <= (double)total * (5.0 + runin / 256.0);
+  return total >= kAdjLeastTotal && (double)(rounds * p.simds * kStripLanes * len) <= (double)total * (5.0 + runin / 256.0);
 }
 
 template <typename F>
@@ -159,43 +159,67 @@ sos_status launch_adj_strip(bool forward, bool adjoint, const sos_plan_s &p, con
                              static_cast<const float *>(gy), static_cast<float *>(gx), ws, s);
 }
 
+// The shortest strips, a multiple of 32 samples from the channels' even share
+// on, for which a wavefront per SIMD serves every channel; at most a wavefront
+// for the longest.  Bisection: the channels' wavefronts, sum ceil(n / 64 len),
+// fall with len and are at least C and at most total / (64 len) + C, so a set of
+// more channels than SIMDs needs none, and one of few channels a step or two.  (A
+// serving loop replans on every request: 3000 channels, the longest 2^23 samples,
+// 15.5 ms with every length tried in turn, 0.7 ms so.)
+int64_t adj_strip_len(const int64_t *n, int C, int64_t total, int64_t longest, int64_t simds) {
+  const int64_t first = std::max(kLeastLen, (total / (simds * kStripLanes) + 31) / 32 * 32);
+  auto up = [&](int64_t len) { return len <= first ? 0 : (len - first + 31) / 32; };   // steps of 32 from the first
+  int64_t lo = 0, hi = up((longest + kStripLanes - 1) / kStripLanes);
+  if (C < simds) hi = std::min(hi, up(total / (kStripLanes * (simds - C)) + 1));
+  else lo = C > simds ? hi : 0;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2, per = kStripLanes * (first + 32 * mid);
+    int64_t waves = 0;
+    for (int c = 0; c < C && waves <= simds; ++c) waves += (n[c] + per - 1) / per;
+    if (waves <= simds) hi = mid;
+    else lo = mid + 1;
+  }
+  return first + 32 * lo;
+}
+
 // Every channel of a batch by strips, or none (the tiles and the strips would
-// run one after the other).  One wavefront per SIMD shares the channels out:
-// the shortest strips for which it does.
+// run one after the other).
 void adj_strip_schedule(sos_batch_s &b, const sos_plan_t *plans) {
   if (!b.adj_rc) return;
-  int64_t total = 0, longest = 0, runin = 0;
-  for (int c = 0; c < b.C; ++c) {
+  int64_t total = 0, runin = 0;
+  int longest = 0;   // place in the launch order
+  for (int i = 0; i < b.C; ++i) {
+    const int32_t c = b.order[i];
     if (!plans[c]->adj_span || b.n[c] < kLeastLen) return;
     total += b.n[c];
-    longest = std::max(longest, b.n[c]);
+    if (b.n[c] > b.n[b.order[longest]]) longest = i;
     runin = std::max(runin, plans[c]->bwd->runin);
   }
+  if (total < kAdjLeastTotal) return;
   const int64_t simds = plans[0]->simds;
-  auto waves_of = [&](int64_t n, int64_t len) { return (n + kStripLanes * len - 1) / (kStripLanes * len); };
-  int64_t len = std::max(kLeastLen, (total / (simds * kStripLanes) + 31) / 32 * 32);
-  for (; len * kStripLanes < longest; len += 32) {
-    int64_t waves = 0;
-    for (int c = 0; c < b.C; ++c) waves += waves_of(b.n[c], len);
-    if (waves <= simds) break;
-  }
+  const int64_t len = adj_strip_len(b.n.data(), b.C, total, b.n[b.order[longest]], simds);
+  auto cut = [&](int i, AdjStrip &d) {
+    const int32_t c = b.order[i];
+    const AdjChan &t = b.adj_chans[i];
+    const int64_t w = (b.n[c] + kStripLanes * len - 1) / (kStripLanes * len), per = kStripLanes * w;
+    return adj_strip_geometry(*plans[c], b.n[c], (int32_t)(b.off[c] % 4), (b.n[c] + per - 1) / per, t.saved_off,
+                              t.partial_off - t.saved_off, d);
+  };
+  // the longest channel's strips alone tell most sets that do not gain
+  AdjStrip one;
+  if (!cut(longest, one) || !adj_strip_pays(*plans[0], runin, total, one.waves, one.c.len)) return;
   std::vector<AdjStrip> strips(b.C);
   std::vector<int32_t> items;
   for (int i = 0; i < b.C; ++i) {
-    const int32_t c = b.order[i];
-    const AdjChan &t = b.adj_chans[i];
     AdjStrip &d = strips[i];
-    const int64_t w = waves_of(b.n[c], len), per = kStripLanes * w;
-    if (!adj_strip_geometry(*plans[c], b.n[c], (int32_t)(b.off[c] % 4), (b.n[c] + per - 1) / per, t.saved_off,
-                            t.partial_off - t.saved_off, d))
-      return;
-    d.c.off = b.off[c];
+    if (!cut(i, d)) return;
+    d.c.off = b.off[b.order[i]];
     d.c.first_item = (int64_t)items.size();
     items.insert(items.end(), (size_t)d.waves, i);
   }
   int64_t most = 0;
   for (const AdjStrip &d : strips) most = std::max(most, d.c.len);
-  if ((int64_t)items.size() > b.adj_strip_room || 
+  if ((int64_t)items.size() > b.adj_strip_room ||
       !adj_strip_pays(*plans[0], runin, total, (int64_t)items.size(), most))
     return;
   for (int i = 0; i < b.C; ++i) {   // the reduction's view

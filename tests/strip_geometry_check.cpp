@@ -3,6 +3,7 @@
 // host-only, with a placeholder for the device tables.  Prints each violation
 // and the number of cuts looked at; exits 1 if there was one.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <vector>
@@ -58,6 +59,47 @@ void check(const sos_plan_s &p, const StripChan &c, int64_t runin) {
   if ((c.strips + 80) * c.len * es >= (int64_t)1 << 32) fail("32-bit offsets", p, c);
 }
 
+// The strip length of a batch's adjoint against every length tried in turn, and
+// a set for which that would take 1e9 divisions.
+void lengths_of_batches() {
+  uint64_t state = 1;
+  auto draw = [&](int64_t lo, int64_t hi) {   // log-uniform
+    state = state * 6364136223846793005ull + 1442695040888963407ull;
+    return (int64_t)std::exp(std::log((double)lo) + (double)(state >> 11) / 9007199254740992.0 * std::log((double)hi / lo));
+  };
+  for (int t = 0; t < 4000; ++t) {
+    const int64_t simds = t % 5 ? 1024 : draw(1, 64);
+    const int C = t % 7 ? (int)draw(1, 300) : (int)(simds + draw(1, 4) - 2 > 0 ? simds + draw(1, 4) - 2 : 1);
+    std::vector<int64_t> n(C);
+    int64_t total = 0, longest = 0;
+    for (int64_t &v : n) {
+      v = draw(64, t % 3 ? 1 << 20 : 1 << 14);
+      total += v;
+      longest = std::max(longest, v);
+    }
+    const int64_t got = adj_strip_len(n.data(), C, total, longest, simds);
+    int64_t len = std::max<int64_t>(64, (total / (simds * 64) + 31) / 32 * 32);
+    for (; len * 64 < longest; len += 32) {
+      int64_t waves = 0;
+      for (int64_t v : n) waves += (v + 64 * len - 1) / (64 * len);
+      if (waves <= simds) break;
+    }
+    if (got != len && ++bad <= 20)
+      std::printf("strip length of %d channels: %lld, in turn %lld\n", C, (long long)got, (long long)len);
+  }
+  std::vector<int64_t> n(5000, 1000);
+  n[7] = (int64_t)1 << 29;
+  const auto start = std::chrono::steady_clock::now();
+  int64_t sum = 0;
+  for (int simds : {1024, 4999, 5000, 5001, 6000, 40000})
+    sum += adj_strip_len(n.data(), 5000, n[7] + 4999000, n[7], simds);
+  const double s = std::chrono::duration<double>(std::chrono::steady_clock::now() - start).count();
+  if (s > 0.1 || sum <= 0) {
+    ++bad;
+    std::printf("strip lengths of 5000 channels took %g s\n", s);
+  }
+}
+
 }  // namespace
 
 int main() {
@@ -97,6 +139,7 @@ int main() {
               if (adj_strip_single(*p, per * p->simds * 64 + off, (size_t)1 << 40, d)) check(*p, d.c, p->bwd->runin);
         }
       }
+  lengths_of_batches();
   std::printf("%lld cuts, shortest strip %lld, %lld bad\n", (long long)looked, (long long)shortest, (long long)bad);
   return bad != 0 || looked < 100000;
 }
