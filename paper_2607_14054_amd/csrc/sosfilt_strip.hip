@@ -309,12 +309,37 @@ sos_status launch_strip(const sos_plan_s &p, const StripChan &c, const void *x, 
   return c.mt == 1 ? launch<double, 1>(a, a.items, c.terms, p.K, x, y, s) : launch<double, 2>(a, a.items, c.terms, p.K, x, y, s);
 }
 
+namespace {
+
+// What a batch's launch takes, in us, by tiles and by strips: fits to 900 random
+// batches of 2 .. 1000 channels of 1000 .. 8e6 samples (1e6 .. 1.5e8 in all, K =
+// 1 .. 16, N = 8 .. 64, poles to r = 0.9 .. 0.999), each timed both ways on
+// MI355X; the ratio of the two is right to 20% (rms).  Tiles: the longest
+// tile's chain with its run-in, K (warm + tile), and the tiles' share of a SIMD,
+// in 1000 section-samples.  Strips: the filter's longest chain, (K + 5) len; the
+// state pass, whose matrix products take as long whatever K, by its longest
+// chain and its share of a SIMD; a third of the memory time is the second read;
+// the scan's launches where run-ins reach over more than 16 strips; the longest
+// chain of a channel that stays with the tiles.
+struct BatchCost {
+  double base, chain, share, chain8, share8;   // tiles (chain8, share8: more at N = 8)
+  double sbase, filter, state, products, rest, scan, memory;
+};
+constexpr BatchCost kBatchCost[2] = {{10.1, 0.99, 0.89, 0.24, 0.27, 6.3, 6.5, 10.1, 11.7, 1.5, 16.4, 0.6},
+                                     {9.4, 1.20, 1.11, 0.42, 0.13, 0.9, 6.3, 16.6, 17.3, 2.7, 11.9, 0.7}};
+
+}  // namespace
+
 // Strips in a batch, where the tiles would spend much of their work on
 // run-ins: 64 channels x 2^20 with poles up to r = 0.999 (FP32, K = 8) take
 // 382 us by tiles and 203 by strips, while a ragged batch with short run-ins
 // (256 channels of 2^10 .. 2^22, K = 1 .. 16, r <= 0.95) is better off with
-// the tiles (438 us against 520).  The line is 1.5 times the channels' own
-// section-samples.  A wavefront of 64 strips costs about (K + 5) len (a chunk
+// the tiles (438 us against 520).  At least 1.5 times the channels' own
+// section-samples, and 1.2 times the time that the strips would take: without
+// the second line 202 of 557 of those 900 batches lost more than 5% (300 channels
+// of 10000 .. 40000 samples, K = 12, r <= 0.9: 58 us by tiles, 87 by strips; one
+// of 6e6 samples in 16 channels, K = 1: 19 and 45), with it one of 243 does (9%).
+// A wavefront of 64 strips costs about (K + 5) len (a chunk
 // that filters nothing takes as long as five sections); the lengths share the
 // long channels' work out to two wavefronts per SIMD.  Channels too short for
 // 64 strips of a sensible length stay with the tiles.
@@ -322,40 +347,63 @@ void strip_schedule(sos_batch_s &b, const sos_plan_t *plans) {
   strip_unschedule(b);
   if (b.block || b.host_only || !b.b0one || b.mix != SOS_PH || b.tile_groups > 0) return;
   constexpr int64_t kLeast = 16384, kLeastTotal = 1 << 22;
-  constexpr double kBase = 5.0, kRunIn = 1.5;
-  double work = 0.0, own = 0.0, tiles = 0.0;
+  constexpr double kBase = 5.0, kRunIn = 1.5, kGain = 1.2;
+  double work = 0.0, own = 0.0, tiles = 0.0, chain = 0.0, share = 0.0;
   int64_t total = 0;
   std::vector<char> takes(b.C, 0);
+  std::vector<double> tile_chain(b.C, 0.0);   // 1000 section-samples
   for (int i = 0; i < b.C; ++i) {
     const int c = b.order[i];
+    const int64_t items = (i + 1 < b.C ? b.chans[i + 1].first_item : b.items) - b.chans[i].first_item;
+    if (items == 0) continue;
+    tile_chain[c] = plans[c]->K * 1e-3 *
+                    (double)(b.tile[c] + std::min<int64_t>(b.chans[i].warm, (b.n[c] - 1) / b.tile[c] * b.tile[c]));
+    chain = std::max(chain, tile_chain[c]);
+    share += (double)items * tile_chain[c];
     takes[c] = plans[c]->d_strip && b.n[c] >= kLeast;
     if (!takes[c]) continue;
-    const int64_t items = (i + 1 < b.C ? b.chans[i + 1].first_item : b.items) - b.chans[i].first_item;
-    const int64_t warm = std::min<int64_t>(b.chans[i].warm, (b.n[c] - 1) / b.tile[c] * b.tile[c]);
-    tiles += (double)items * (64 / b.L) * plans[c]->K * (double)(b.tile[c] + warm);
+    tiles += (double)items * (64 / b.L) * 1e3 * tile_chain[c];
     own += (double)b.n[c] * plans[c]->K;
     work += (double)b.n[c] * (plans[c]->K + kBase);
     total += b.n[c];
   }
   if (total < kLeastTotal || tiles < kRunIn * own) return;
-  const double quota = work / (2.0 * plans[0]->simds * kStripLanes);   // a lane's share
+  const double simds = plans[0]->simds, quota = work / (2.0 * simds * kStripLanes);   // a lane's share
   const int64_t V = b.io_dtype == SOS_F64 ? 2 : 4;
   std::vector<StripChan> chans;
   std::vector<double> cost;
+  double filter = 0.0, state = 0.0, products = 0.0, rest = 0.0;
+  bool scan = false;
   for (int c = 0; c < b.C; ++c) {
-    if (!takes[c]) continue;
+    if (!takes[c]) {
+      rest = std::max(rest, tile_chain[c]);
+      continue;
+    }
     const int64_t n = b.n[c], want = std::max<int64_t>((int64_t)(quota / (plans[c]->K + kBase)), 64);
     const int64_t w = std::max<int64_t>((n + 64 * want / 2) / (64 * want), 1);   // wavefronts of the channel
     StripChan s{};
     if (!strip_geometry(*plans[c], n, (int32_t)(b.off[c] % V), (n + 64 * w - 1) / (64 * w), s)) {
       takes[c] = 0;
+      rest = std::max(rest, tile_chain[c]);
       continue;
     }
     s.off = b.off[c];
     chans.push_back(s);
     cost.push_back((s.K + kBase) * (double)s.len);
+    const double mfma = 1e-3 * (double)s.span * s.mt * (s.terms > 1 ? 5 : 4);   // 16-strip tiles of the state pass
+    filter = std::max(filter, 1e-3 * cost.back());
+    state = std::max(state, mfma);
+    products += mfma * (double)((s.strips + kStripLanes - 1) / kStripLanes);
+    scan = scan || s.terms > 16;
   }
   if (chans.empty()) return;
+  const BatchCost &m = kBatchCost[b.io_dtype == SOS_F64];
+  const double by_tiles = m.base + (m.chain + (b.N == 8 ? m.chain8 : 0.0)) * chain +
+                          (m.share + (b.N == 8 ? m.share8 : 0.0)) * share / simds;
+  const double mb = 1e-6 * (double)b.total * (b.io_dtype == SOS_F64 ? 8 : 4);
+  const double by_strips = m.sbase + m.filter * filter + m.state * state + m.products * products / (2.0 * simds) +
+                           m.rest * rest + (scan ? m.scan : 0.0) + m.memory * mb;
+  if (by_tiles < kGain * by_strips) return;
   // costliest wavefronts first
   std::vector<int32_t> order(chans.size());
   std::iota(order.begin(), order.end(), 0);

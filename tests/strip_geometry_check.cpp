@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <vector>
 
+#include "../paper_2607_14054_amd/csrc/batch.hpp"
 #include "../paper_2607_14054_amd/csrc/plan.hpp"
 #include "../paper_2607_14054_amd/csrc/strip_types.hpp"
 
@@ -100,6 +101,45 @@ void lengths_of_batches() {
   }
 }
 
+// The route of batches timed both ways on MI355X (us by tiles / by strips):
+// strips where they gain, and only there.
+void routes_of_batches() {
+  struct Set {
+    int C;
+    int64_t lo, hi;
+    int K, io, N;
+    double r;
+    bool strips;
+  };
+  const Set sets[] = {{16, 191977, 639924, 1, SOS_F32, 32, 0.9, false},      // 19 / 45
+                      {265, 11321, 37739, 2, SOS_F32, 64, 0.98, false},      // 36 / 81
+                      {300, 10000, 40000, 12, SOS_F32, 32, 0.9, false},      // 58 / 87
+                      {99, 3095, 154758, 6, SOS_F64, 32, 0.9, false},        // 48 / 78
+                      {54, 247306, 274785, 6, SOS_F32, 32, 0.95, false},     // 63 / 92
+                      {64, 1 << 20, 1 << 20, 8, SOS_F32, 32, 0.999, true},   // 382 / 203
+                      {13, 586752, 586752, 12, SOS_F32, 8, 0.999, true},     // 939 / 110
+                      {40, 103368, 344561, 8, SOS_F64, 16, 0.999, true}};    // 604 / 106
+  for (const Set &t : sets) {
+    sos_plan_t p = make(t.K, t.r, t.io, t.N);
+    std::vector<sos_plan_t> plans(t.C, p);
+    std::vector<int64_t> n(t.C);
+    for (int c = 0; c < t.C; ++c) n[c] = t.lo + (t.hi - t.lo) * c / t.C;
+    sos_batch_opts o{0, SOS_FLAG_HOST_ONLY, 0, 0, 0};
+    sos_batch_t b = nullptr;
+    if (sos_batch_plan(plans.data(), t.C, n.data(), nullptr, &o, &b) != SOS_OK) std::abort();
+    const std::vector<int32_t> tiles = b->item_chan;
+    b->host_only = false;   // schedule as a device batch
+    strip_schedule(*b, plans.data());
+    if ((b->strip_items > 0) != t.strips && ++bad)
+      std::printf("%d channels of %lld .. %lld, K %d: %s\n", t.C, (long long)t.lo, (long long)t.hi, t.K,
+                  b->strip_items > 0 ? "strips" : "tiles");
+    strip_unschedule(*b);
+    if ((b->item_chan != tiles || b->rows_items != b->items) && ++bad) std::printf("the tiles' items are not back\n");
+    b->host_only = true;
+    sos_batch_destroy(b);
+  }
+}
+
 }  // namespace
 
 int main() {
@@ -140,6 +180,7 @@ int main() {
         }
       }
   lengths_of_batches();
+  routes_of_batches();
   std::printf("%lld cuts, shortest strip %lld, %lld bad\n", (long long)looked, (long long)shortest, (long long)bad);
   return bad != 0 || looked < 100000;
 }
