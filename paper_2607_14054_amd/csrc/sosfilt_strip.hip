@@ -263,6 +263,14 @@ bool strip_single(const sos_plan_s &p, int64_t n, int64_t tile, bool scan, Strip
   if (f64 && (!wide || K <= 6)) most = 30000000;
   if (!f64 && !wide && K <= 6) most = 40000000;
   if (n < least || n > most) return false;
+  // A lone section is bound by memory either way, and the strips' state pass reads
+  // x again: all of it where the run-in is longer than the state table.  That pays
+  // against tiles that spend several of their lengths on run-ins, and otherwise
+  // only where N = 64 shares odd sizes out unevenly (FP32, K = 1, N = 64, run-in
+  // 1419, 3.4e7 samples: tiles 72 us, strips 111; 3019, 2.25e8: 417 and 625; N =
+  // 32, run-in 161, 2.3e7: 38 and 46; run-in 9005, 2.5e7: 126 and 88.  The means of
+  // 8 and 7 such sizes: strips 1.16 and 1.10 times as long).
+  if (!f64 && !scan && K == 1 && p.runin < 4000 && (!wide || p.runin > p.strip_span)) return false;
   const int64_t lanes = (int64_t)p.simds * 64, groups = tile / ((int64_t)p.N * p.L);
   if (!f64 && !scan && (groups & (groups - 1)) == 0 && n % (tile * 4 * p.simds) == 0) return false;
   return strip_geometry(p, n, 0, (n + lanes - 1) / lanes, c);

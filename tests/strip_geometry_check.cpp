@@ -140,6 +140,27 @@ void routes_of_batches() {
   }
 }
 
+// Single signals of one section (FP32): strips only with N = 64 and a run-in that
+// the state table covers or that takes the tiles several of their lengths.
+void routes_of_one_section() {
+  struct Signal {
+    int K, N;
+    double r;
+    int64_t n;
+    bool strips;
+  };
+  for (const Signal &t : {Signal{1, 64, 0.99, 225000001, false}, Signal{1, 32, 0.85, 23000001, false},
+                          Signal{1, 64, 0.9, 34000001, true}, Signal{1, 64, 0.996, 27000001, true},
+                          Signal{1, 32, 0.997, 24700001, true}, Signal{2, 64, 0.99, 33500001, true},
+                          Signal{2, 32, 0.9, 31000001, true}}) {
+    sos_plan_t p = make(t.K, t.r, SOS_F32, t.N);
+    StripChan c;
+    if (strip_single(*p, t.n, 3 * 16 * t.N, false, c) != t.strips && ++bad)
+      std::printf("K %d N %d run-in %lld n %lld: not %s\n", t.K, t.N, (long long)p->runin, (long long)t.n,
+                  t.strips ? "strips" : "tiles");
+  }
+}
+
 }  // namespace
 
 int main() {
@@ -181,6 +202,7 @@ int main() {
       }
   lengths_of_batches();
   routes_of_batches();
+  routes_of_one_section();
   std::printf("%lld cuts, shortest strip %lld, %lld bad\n", (long long)looked, (long long)shortest, (long long)bad);
   return bad != 0 || looked < 100000;
 }
