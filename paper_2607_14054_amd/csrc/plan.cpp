@@ -42,13 +42,16 @@ double inf_norm(const std::vector<double> &M, int n) {
   return best;
 }
 
+// Product of two transitions.  A section's state depends on its own and on those
+// of the sections before it, so they are block lower triangular (2 x 2 blocks),
+// and only the blocks on and below the diagonal are formed.
 std::vector<double> matmul(const std::vector<double> &A, const std::vector<double> &B, int n) {
   std::vector<double> C(n * n, 0.0);
   for (int i = 0; i < n; ++i)
-    for (int k = 0; k < n; ++k) {
+    for (int k = 0; k < (i | 1) + 1; ++k) {
       double a = A[i * n + k];
       if (a == 0.0) continue;
-      for (int j = 0; j < n; ++j) C[i * n + j] += a * B[k * n + j];
+      for (int j = 0; j < (k | 1) + 1; ++j) C[i * n + j] += a * B[k * n + j];
     }
   return C;
 }

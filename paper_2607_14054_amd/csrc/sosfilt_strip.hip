@@ -22,13 +22,48 @@ bool strip_supported(const sos_plan_s &p) {
 
 namespace {
 
-// phi_pow again, each power the square of the one before in extended
-// precision, rounded to FP64 at the end.  A section's state depends on its
-// own and on those of the sections before it, so the matrices are block lower
-// triangular and a product needs only the blocks on and below the diagonal.
+#if defined(__x86_64__)
+typedef double v4d __attribute__((vector_size(32)));
+
+// (ch, cl) = (hi, lo)^2, block lower triangular, in rows of ld doubles (a multiple
+// of 4), each entry an unevaluated sum of two FP64 numbers: the rounding errors of
+// the products (by FMA) and of the sums (Knuth's two-sum) are FP64 numbers too, and
+// go into the low part.
+__attribute__((target("avx2,fma"))) void square_pairs(const double *hi, const double *lo, double *ch, double *cl,
+                                                      int D, int ld) {
+#pragma clang fp contract(off)
+  for (int i = 0; i < D; i += 2)
+    for (int j = 0; j < i + 2; j += 4) {
+      v4d sh[2] = {}, sl[2] = {};
+      for (int k = j; k < i + 2; ++k) {
+        v4d bh, bl;
+        __builtin_memcpy(&bh, hi + k * ld + j, 32);
+        __builtin_memcpy(&bl, lo + k * ld + j, 32);
+        for (int r = 0; r < 2; ++r) {
+          const double x = hi[(i + r) * ld + k], y = lo[(i + r) * ld + k];
+          const v4d ah = {x, x, x, x}, al = {y, y, y, y};
+          const v4d p = ah * bh, e = __builtin_elementwise_fma(ah, bh, -p);
+          const v4d s = sh[r] + p, t = s - sh[r];
+          sl[r] += (ah * bl + al * bh) + (e + ((sh[r] - (s - t)) + (p - t)));
+          sh[r] = s;
+        }
+      }
+      for (int r = 0; r < 2; ++r) {
+        const v4d h = sh[r] + sl[r], l = sl[r] - (h - sh[r]);
+        __builtin_memcpy(ch + (i + r) * ld + j, &h, 32);
+        __builtin_memcpy(cl + (i + r) * ld + j, &l, 32);
+      }
+    }
+}
+#endif
+
+// phi_pow again, each power the square of the one before in more than FP64
+// precision, rounded to FP64 at the end.  The matrices are block lower triangular,
+// as in the plan's own products.  Pairs of FP64 numbers where the CPU has FMA: the
+// x87 products of one sum wait for each other (K = 16: 120 us of a plan's 345).
 void square_powers(sos_plan_s &p) {
   const int D = 2 * p.K;
-  std::vector<long double> a(p.phi.begin(), p.phi.end()), b((size_t)D * D);
+  std::vector<long double> a(p.phi.begin(), p.phi.end());
   // the one-step transition's last row of each section, from the coefficients
   // (its entries are short sums that FP64 rounds)
   for (int col = 0; col < D; ++col) {
@@ -43,6 +78,26 @@ void square_powers(sos_plan_s &p) {
       now = yn;
     }
   }
+#if defined(__x86_64__)
+  if (__builtin_cpu_supports("avx2") && __builtin_cpu_supports("fma")) {
+    const int ld = (D + 3) & ~3;
+    std::vector<double> m(4 * (size_t)D * ld, 0.0);
+    double *hi = m.data(), *lo = hi + D * ld, *ch = lo + D * ld, *cl = ch + D * ld;
+    for (int i = 0; i < D; ++i)
+      for (int j = 0; j < D; ++j) {
+        hi[i * ld + j] = (double)a[(size_t)i * D + j];
+        lo[i * ld + j] = (double)(a[(size_t)i * D + j] - hi[i * ld + j]);
+      }
+    for (size_t q = 1; q < p.phi_pow.size(); ++q) {
+      square_pairs(hi, lo, ch, cl, D, ld);
+      std::swap(hi, ch);
+      std::swap(lo, cl);
+      for (int i = 0; i < D; ++i) std::copy(hi + i * ld, hi + i * ld + D, p.phi_pow[q].begin() + (size_t)i * D);
+    }
+    return;
+  }
+#endif
+  std::vector<long double> b((size_t)D * D, 0.0L);
   for (size_t q = 1; q < p.phi_pow.size(); ++q) {
     for (int i = 0; i < D; ++i)
       for (int j = 0; j < (i | 1) + 1; ++j) {

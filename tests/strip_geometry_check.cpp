@@ -161,6 +161,51 @@ void routes_of_one_section() {
   }
 }
 
+// FP64 plans' powers of the transition, Phi^(2^j), against squares in 113 bits of
+// the same one-step transition (64 bits, from the coefficients).  Pairs of FP64
+// numbers lose at most 32 * 2^-104 of the summands' size per square, which 13
+// squares double to 2^-86, far below the last rounding: half a unit of the largest
+// entry, and one for the pairs.  Plain FP64 squares are 2^-53 off at the first.
+void powers_of_the_transition() {
+  typedef __float128 q;
+  for (int K : {1, 3, 8, 12, 15, 16})
+    for (double r : {0.3, 0.9, 0.999}) {
+      sos_plan_t p = make(K, r, SOS_F64, 32);
+      p->d_strip = nullptr;
+      (void)upload_strip(*p);   // (the tables' upload itself needs a GPU)
+      const int D = 2 * K;
+      std::vector<q> a(D * D), b(D * D);
+      for (int col = 0; col < D; ++col) {
+        long double in2 = 0, in1 = 0, now = 0;
+        for (int k = 0; k < K; ++k) {
+          const double *o = &p->rows[5 * k];
+          const long double y2 = col == 2 * k, y1 = col == 2 * k + 1;
+          const long double yn = o[0] * now + o[1] * in1 + o[2] * in2 - o[3] * y1 - o[4] * y2;
+          a[2 * k * D + col] = y1;
+          a[(2 * k + 1) * D + col] = yn;
+          in2 = y2;
+          in1 = y1;
+          now = yn;
+        }
+      }
+      for (size_t j = 1; j < p->phi_pow.size(); ++j) {
+        for (int i = 0; i < D; ++i)
+          for (int c = 0; c < D; ++c) {
+            q sum = 0;
+            for (int k = 0; k < D; ++k) sum += a[i * D + k] * a[k * D + c];
+            b[i * D + c] = sum;
+          }
+        a.swap(b);
+        double most = 0, off = 0;
+        for (int i = 0; i < D * D; ++i) {
+          most = std::max(most, std::fabs((double)a[i]));
+          off = std::max(off, std::fabs((double)((q)p->phi_pow[j][i] - a[i])));
+        }
+        if (!(off <= most * 0x1p-52) && ++bad) std::printf("K %d r %g Phi^(2^%d): %g of %g off\n", K, r, (int)j, off, most);
+      }
+    }
+}
+
 }  // namespace
 
 int main() {
@@ -203,6 +248,7 @@ int main() {
   lengths_of_batches();
   routes_of_batches();
   routes_of_one_section();
+  powers_of_the_transition();
   std::printf("%lld cuts, shortest strip %lld, %lld bad\n", (long long)looked, (long long)shortest, (long long)bad);
   return bad != 0 || looked < 100000;
 }
