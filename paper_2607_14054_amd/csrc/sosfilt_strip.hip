@@ -121,7 +121,10 @@ void square_powers(sos_plan_s &p) {
 //     order the products read them, [block][row tile][pair][lane][2], lane
 //     (i, q) of pair k holding row i, elements 4 q + 2 k and the next;
 //   all-pole responses g_k: section k's output to a unit input of the first
-//     section's recursive part (h_k = g_k + b1 g_k[. - 1] + b2 g_k[. - 2]).
+//     section's recursive part.  (h_k = g_k + b1 g_k[. - 1] + b2 g_k[. - 2], but
+//     that sum cancels digits where the first section's zeros lie near slow poles:
+//     FP64, K = 11, poles to r = 0.999: results 1e-10 off where the recurrence
+//     itself is 3e-12 off.  So h_k is the whole cascade's own response.)
 sos_status upload_strip(sos_plan_s &p) {
   const int K = p.K, D = 2 * K, mt = (D + 15) / 16, R = 16 * mt;
   auto covering = [](int64_t runin) { return (int)std::min<int64_t>((runin + 31) / 32 * 32, kStripMaxSpan); };
@@ -131,41 +134,30 @@ sos_status upload_strip(sos_plan_s &p) {
   const size_t hop = (size_t)span * R, gsz = (size_t)K * gs, psz = p.phi_pow.size() * (size_t)R * R;
   std::vector<double> t((hop + psz) * (p.adj_span ? 2 : 1) + gsz, 0.0);
   double *g = t.data() + hop, *ph = g + gsz;
-  // every section per sample, so that the sections' recurrences overlap
-  std::vector<double> state(4 * (size_t)K, 0.0);   // per section: input x1, x2, output y1, y2
+  // both responses (g_k, h_k) side by side, every section per sample, so that the
+  // sections' recurrences overlap
+  typedef double v2d __attribute__((vector_size(16)));
+  std::vector<v2d> state(4 * (size_t)K, v2d{0.0, 0.0});   // per section: input x1, x2, output y1, y2
   for (int j = 0; j < gs; ++j) {
-    double v = j == 0 ? 1.0 : 0.0;   // the first section's recursive part takes it as it is
+    v2d v = j == 0 ? v2d{1.0, 1.0} : v2d{0.0, 0.0};
+    const int e = 15 - j % 16;
+    double *blk = &t[(size_t)(j / 16) * (16 * R) + ((e % 4 / 2) * 64 + e / 4 * 16) * 2 + e % 2];
     for (int k = 0; k < K; ++k) {
-      const double *o = &p.rows[5 * k];
-      double *z = &state[4 * (size_t)k];
-      if (k > 0) {
-        const double x0 = v;
-        v = x0 + o[1] * z[0] + o[2] * z[1];
-        z[1] = z[0];
-        z[0] = x0;
-      }
+      const double *o = &p.rows[5 * k], on = k > 0 ? 1.0 : 0.0;   // g_0: the first section's recursive part alone
+      v2d *z = &state[4 * (size_t)k];
+      const v2d x0 = v;
+      v = x0 + v2d{on * o[1], o[1]} * z[0] + v2d{on * o[2], o[2]} * z[1];
+      z[1] = z[0];
+      z[0] = x0;
       v -= o[3] * z[2] + o[4] * z[3];
+      if (j < span) {
+        double *at = blk + ((2 * k) / 16 * 128 + (2 * k) % 16) * 2;
+        at[0] = z[2][1];   // d = 1: h_k[j - 1]
+        at[2] = v[1];      // d = 0: h_k[j]
+      }
       z[3] = z[2];
       z[2] = v;
-      g[(size_t)k * gs + j] = v;
-    }
-  }
-  const double b1 = p.rows[1], b2 = p.rows[2];
-  std::vector<double> h(span + 1);
-  for (int k = 0; k < K; ++k) {
-    const double *gk = g + (size_t)k * gs;
-    h[0] = 0.0;   // h[l + 1] = h_k[l]
-    h[1] = gk[0];
-    if (span > 1) h[2] = gk[1] + b1 * gk[0];
-    for (int l = 2; l < span; ++l) h[l + 1] = gk[l] + b1 * gk[l - 1] + b2 * gk[l - 2];
-    for (int b = 0; b < span / 16; ++b) {
-      const double *hb = &h[16 * b];
-      const int i = (2 * k) % 16;
-      for (int e = 0; e < 16; ++e) {
-        double *at = &t[(size_t)b * (16 * R) + (((2 * k) / 16 * 2 + e % 4 / 2) * 64 + e / 4 * 16 + i) * 2 + e % 2];
-        at[0] = hb[15 - e];   // d = 1: h_k[j - 1]
-        at[2] = hb[16 - e];   // d = 0: h_k[j]
-      }
+      g[(size_t)k * gs + j] = v[0];
     }
   }
   // FP64 I/O: the powers squared in extended precision.  Repeated FP64
