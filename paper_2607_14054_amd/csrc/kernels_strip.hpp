@@ -216,7 +216,8 @@ __device__ __forceinline__ void strip_transitions(double (&P)[4][1][4], const do
 // consecutive samples (element e of the four lanes q of a strip make one
 // product step) and the table is laid out to match.
 //
-// SCAN (strips shorter than the run-in, len = 2^lg): the end states of the
+// SCAN (strips shorter than the run-in; len is 2^lg, or for MT = 1 and up to 16
+// strips' sums any multiple of 32, see strip_transitions): the end states of the
 // 16 strips before come along as one more tile, and log2 doubling rounds
 // make every end state the sum over up to 16 strips; the product's output
 // layout is the next product's input layout, so that the states stay in

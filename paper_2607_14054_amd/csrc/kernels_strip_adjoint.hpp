@@ -161,6 +161,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 1) void strip_adjoint_kernel(c
   typedef StripStage<TI> St;
   typedef typename St::VT VT;
   constexpr int V = St::V, C = St::C, K = kAdjStripK, SUBS = C / kAdjC, PP = kAdjC / V;   // PP: pieces per 16 samples
+  static_assert(sizeof(TI) == 4 && SUBS == 2, "FP32 I/O: 32 samples and K = 8 sections' states per line");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   AdjStrip d;
@@ -203,7 +204,8 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 1) void strip_adjoint_kernel(c
   }
   const int chunks = (int)(c.len / C), head = s0 == 0 && c.shift > 0 ? c.lead / C : -1;   // uniform
   sv4u ix[St::OPS], ig[St::OPS], is[St::OPS];
-  VT hist;   // x[t-2], x[t-1] before the chunk (FP32: in the first two)
+  typedef float v2f __attribute__((ext_vector_type(2)));
+  v2f hist;   // x[t-2], x[t-1] before the chunk
   auto fetch = [&](int ch) {
 #pragma unroll
     for (int j = 0; j < St::OPS; ++j) {
@@ -212,15 +214,8 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 1) void strip_adjoint_kernel(c
       ig[j] = __builtin_bit_cast(sv4u, __builtin_amdgcn_raw_buffer_load_b128(rg, o, 0, 0));
       is[j] = __builtin_bit_cast(sv4u, __builtin_amdgcn_raw_buffer_load_b128(rc, o, 0, 0));
     }
-    const uint32_t o = mine + 128u * (uint32_t)ch - 2u * (uint32_t)sizeof(TI);
-    if constexpr (sizeof(TI) == 4) {
-      typedef float v2f __attribute__((ext_vector_type(2)));
-      const v2f p = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(rx, o, 0, 0));
-      hist[0] = p[0];
-      hist[1] = p[1];
-    } else {
-      hist = __builtin_bit_cast(VT, __builtin_amdgcn_raw_buffer_load_b128(rx, o, 0, 0));
-    }
+    hist = __builtin_bit_cast(
+        v2f, __builtin_amdgcn_raw_buffer_load_b64(rx, mine + 128u * (uint32_t)ch - 2u * (uint32_t)sizeof(TI), 0, 0));
   };
   VT firsts = {};
   auto chunk = [&](int ch) {
@@ -258,7 +253,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 1) void strip_adjoint_kernel(c
 #pragma unroll
       for (int k = 0; k < K; ++k) st[k] = ts[St::slot(lane, k)];
       double X[kAdjC], q2 = h2, q1 = h1;
-      if (SUBS > 1 && sub > 0) {
+      if (sub > 0) {
         // the chunk's second half starts where the first one ends
         read16(X, tx, 0);
         double p2 = q2, p1 = q1;
