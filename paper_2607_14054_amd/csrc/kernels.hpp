@@ -617,20 +617,15 @@ struct BatchChan {
   int32_t mix;              // SOS_CR / SOS_PH when every section uses it, else SOS_AUTO
 };
 
-// hdr: the batch's device header, hdr[0] the live item count (the grid is
-// sized for the batch's room, so that one launch, captured once, serves
-// every channel set the batch is replanned to).
-template <int N, typename TI, typename T, bool B0ONE, int SOLVER, int L = kL>
-__global__ __launch_bounds__(kWavesPerBlock * 64) void sos_rows_batched_kernel(
-    const TI *__restrict__ x, TI *__restrict__ y, const BatchChan *__restrict__ chans,
-    const int32_t *__restrict__ item_chan, const int64_t *__restrict__ hdr, int32_t kmax) {
+// One item, on wave w of its workgroup.
+template <int N, typename TI, typename T, bool B0ONE, int SOLVER, int L>
+__device__ __forceinline__ void batched_rows(const TI *__restrict__ x, TI *__restrict__ y,
+                                             const BatchChan *__restrict__ chans,
+                                             const int32_t *__restrict__ item_chan, int64_t item, int w,
+                                             int32_t kmax, unsigned char *smem) {
   constexpr int R = 64 / L;   // rows (tiles) per wave
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   TI *stage = reinterpret_cast<TI *>(smem);
   T *state = reinterpret_cast<T *>(smem + stage_bytes<N, TI, L>());
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + w;
-  if (item >= hdr[0]) return;   // uniform per wave
   const BatchChan &ch = chans[item_chan[item]];
   const int64_t quad = item - ch.first_item;
   // the tiles cover [-shift, n), so that with x and y 16-byte aligned every
@@ -661,6 +656,25 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void sos_rows_batched_kernel(
     else SOSF_BATCH_ROWS(SOS_AUTO);
   }
 #undef SOSF_BATCH_ROWS
+}
+
+// hdr: the batch's device header, hdr[0] the live item count (the grid is
+// sized for the batch's room, so that one launch, captured once, serves
+// every channel set the batch is replanned to).
+template <int N, typename TI, typename T, bool B0ONE, int SOLVER, int L = kL>
+__global__ __launch_bounds__(kWavesPerBlock * 64) void sos_rows_batched_kernel(
+    const TI *__restrict__ x, TI *__restrict__ y, const BatchChan *__restrict__ chans,
+    const int32_t *__restrict__ item_chan, const int64_t *__restrict__ hdr, int32_t kmax) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + w;
+  if (item >= hdr[0]) return;   // uniform per wave
+  // FP32 I/O takes w anew, FP64 does not: the three instructions move the loop
+  // against its 64-byte lines, and the two types' loops fall differently (FP64, N =
+  // 64, K = 8, 74 channels of 160000: 114 us without, 120 with; FP32, N = 32, 64
+  // channels of 1000 .. 16000: 48.3 without, 47.4 with; N = 64: 163 and 161).
+  const int wave = sizeof(TI) == 4 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : w;
+  batched_rows<N, TI, T, B0ONE, SOLVER, L>(x, y, chans, item_chan, item, wave, kmax, smem);
 }
 
 }  // namespace sosf

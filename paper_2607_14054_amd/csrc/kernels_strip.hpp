@@ -714,27 +714,6 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_filter_kernel(co
   strip_filter<TI, KT>(xs, ys, c, (item - c.first_item) * kStripLanes, smem + (size_t)w * StripStage<TI>::BYTES);
 }
 
-// One item of the channels that stay with the tiles, on wave w of its workgroup:
-// sos_rows_batched_kernel's work for PH and b0 factored out.  (Its own text: with
-// a function for both, that kernel's N = 64 FP64 instance grew by 12 bytes, its
-// loop moved off its alignment, and 74 channels of 160000 samples, K = 8, took
-// 120 us instead of 114.)
-template <int N, typename TI>
-__device__ __forceinline__ void strip_rows_item(const TI *xs, TI *ys, const BatchChan &ch, int64_t item, int w,
-                                                int32_t kmax, unsigned char *smem) {
-  constexpr int R = 64 / kL;
-  const int64_t quad = item - ch.first_item, ntiles = (ch.n + ch.shift + ch.tile - 1) / ch.tile;
-  const int row = lane_id() / kL;
-  const int64_t t0 = (quad * R + row) * ch.tile - ch.shift;
-  const int64_t last = (quad * R + R - 1 < ntiles - 1 ? quad * R + R - 1 : ntiles - 1);
-  const int64_t warm = ch.warm < last * ch.tile ? ch.warm : last * ch.tile;
-  double *st = reinterpret_cast<double *>(smem + stage_bytes<N, TI, kL>()) + (int64_t)(w * R + row) * state_elems(kmax);
-  TI *buf = reinterpret_cast<TI *>(smem) + (w * R + row) * Stage<N, TI, kL>::ROWBUF;
-  filter_rows<N, TI, double, true, SOS_PH, kL>(xs + ch.off, ys + ch.off, as_ctab(static_cast<const double *>(ch.tab)),
-                                               ch.solver, ch.n, ch.K, ch.stride, t0, warm, ch.tile, true, ch.gain, st,
-                                               buf);
-}
-
 // Batches: the last workgroups, as many as the live strips need, take 64 strips
 // per wavefront; all before them filter the channels that stay with the tiles
 // (their serial chains start first and finish beside the strips), in turn where
@@ -752,7 +731,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void strip_batched_kernel(
   if ((int)blockIdx.x < rows_blocks) {
     const int64_t step = (int64_t)rows_blocks * kWavesPerBlock;
     for (int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + w; item < hdr[0]; item += step)
-      strip_rows_item<N, TI>(xs, ys, chans[item_chan[item]], item, w, kmax, smem);
+      batched_rows<N, TI, double, true, SOS_PH, kL>(xs, ys, chans, item_chan, item, w, kmax, smem);
     return;
   }
   const int64_t item = (int64_t)((int)blockIdx.x - rows_blocks) * kWavesPerBlock + w;
