@@ -157,6 +157,13 @@ typedef struct {
  * here: a level whose r^(2^i) < 2^-60 is flushed to zero coupling; a section
  * with any |f/e|, |c| or |d| above 64 at a remaining level is solved with PH
  * (reported by sos_plan_query).  No division happens on the device.
+ *
+ * Device memory: the tables above (some 20 to 60 KB), the adjoint's, and for
+ * plans that sos_filt, a batch or the adjoint may cut into strips (see
+ * sos_workspace_size) the strips' tables, 8 (16 ceil(K / 8) + K) bytes per
+ * sample of the run-in, up to 1024, and the transition's powers; the first twice
+ * with FP32 I/O and K = 8.  K = 8, poles to r = 0.95: 206 KB in all; FP64 I/O, K
+ * = 16: up to 518 KB.
  */
 sos_status sos_plan(const double *sos, int32_t K, const sos_opts *opts, sos_plan_t *out);
 
@@ -235,9 +242,12 @@ sos_status sos_plan_table(sos_plan_t plan, int32_t table, int32_t section,
  * that the scan's extra launches cost more), or always with
  * SOS_FLAG_CARRY_SCAN; never with SOS_FLAG_CARRY_RUNIN.  Long signals of
  * SOS_AUTO plans without those flags (FP64 arithmetic, K <= 16, L = 16, N = 8 ..
- * 64, no tile_groups) are cut into strips instead, one per lane, with exact
- * start states to the run-in's bound, where that is faster; strips need no
- * workspace, and the size stays the same.
+ * 64, no tile_groups) are cut into strips instead, one per lane, where that is
+ * faster.  A strip's start state sums the history over at least the run-in
+ * before it is rounded to groups (as the run-in does, and the exact carry,
+ * whose scan stops where the transition's norm is below the same bound): what
+ * lies further back, a NaN or Inf included, does not reach it.  Strips need no
+ * workspace; the size stays the same.
  */
 size_t sos_workspace_size(sos_plan_t plan, int64_t n);
 
@@ -288,8 +298,10 @@ sos_status sos_filt_static(sos_plan_t plan, const void *x, void *y, int64_t n, s
  * same tile kernels (Sections V to VII) run on every channel, and only the
  * scheduling is shared: each channel is cut into tiles, four tiles form one
  * wavefront's work item, and the items of all channels are launched
- * together, costliest first.  (SOS_AUTO plans with long run-ins go by strips,
- * as in sos_filt, 64 strips to a work item.)
+ * together, costliest first.  (Where the estimated times of both favour it, the
+ * long channels of a set with long run-ins go by strips, as in sos_filt, 64
+ * strips to a work item: SOS_AUTO plans without a carry flag or tile_groups, in a
+ * batch without reservation or tile_groups.)
  *
  * sos_batch_plan -- fix the channel set and lengths once (allocates).
  *
@@ -377,7 +389,8 @@ sos_status sos_batch_replan(sos_batch_t batch, const sos_plan_t *plans, int32_t 
  * sos_batch_query -- the schedule, for inspection and tests.  Every output
  * pointer is host memory and may be NULL.
  * total     samples spanned by the concatenated buffers (max offset + n).
- * items     wavefront work items (4 tiles each) of the launch.
+ * items     wavefront work items (4 tiles each) of the launch; like tile and
+ *           order, what it is by tiles where channels go by strips.
  * offsets   [C]: first sample of each channel.
  * tile      [C]: samples per tile of each channel (a multiple of 16 N).
  * order     [C]: channel indices in launch order (costliest items first).
@@ -387,7 +400,8 @@ sos_status sos_batch_query(sos_batch_t batch, int64_t *total, int64_t *items, in
 
 /*
  * sos_filt_batched -- y_c = cascade_c(x_c) for every channel, zero initial
- * state, one kernel launch on `stream`.
+ * state: one kernel launch on `stream`, or two, or four, where channels go by
+ * strips (their start states, the sums over more than 16 strips, the filter).
  *
  * x, y       device, `total` samples of the plans' io_dtype each, channel c
  *            at its offset; 16-byte aligned; must not overlap.  Samples of
@@ -487,7 +501,7 @@ sos_status sos_filt_backward_stored(sos_plan_t plan, const void *x, const void *
  * Batched adjoint: sos_filt_backward for every channel of a device batch in
  * three launches (the forward pass that saves the section outputs or the
  * group states, the reversed-time adjoint, the reduction of the coefficient
- * sums).  One mode for the whole batch: saved outputs if any channel's plan
+ * sums), or five by strips (the start states of either direction before them).  One mode for the whole batch: saved outputs if any channel's plan
  * has SOS_FLAG_ADJ_SAVE, else recompute if any has SOS_FLAG_ADJ_RECOMPUTE,
  * else the cheaper by the costs above summed over the channels' samples.
  *

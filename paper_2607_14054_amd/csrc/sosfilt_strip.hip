@@ -393,7 +393,7 @@ constexpr BatchCost kBatchCost[2] = {{10.1, 0.99, 0.89, 0.24, 0.27, 6.3, 6.5, 10
 // section-samples, and 1.2 times the time that the strips would take: without
 // the second line 202 of 557 of those 900 batches lost more than 5% (300 channels
 // of 10000 .. 40000 samples, K = 12, r <= 0.9: 58 us by tiles, 87 by strips; one
-// of 6e6 samples in 16 channels, K = 1: 19 and 45), with it one of 243 does (9%).
+// of 6e6 samples in 16 channels, K = 1: 19 and 45), with it none of 242 did.
 // A wavefront of 64 strips costs about (K + 5) len (a chunk
 // that filters nothing takes as long as five sections); the lengths share the
 // long channels' work out to two wavefronts per SIMD.  Channels too short for
